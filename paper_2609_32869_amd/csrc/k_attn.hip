@@ -708,19 +708,12 @@ __device__ __forceinline__ void op_apply(const OprojArgs& op, int head, int g, i
 //   output       waves summed in LDS; one chunk: O / l, else the chunk's
 //                (max, l, O) record for the merge kernel.
 
-__device__ __forceinline__ bf16x8 pack_bf16x8(const uint32_t* b) {
-  return __builtin_bit_cast(bf16x8, make_uint4(b[0] | b[1] << 16, b[2] | b[3] << 16, b[4] | b[5] << 16, b[6] | b[7] << 16));
-}
 // v = hi + lo: hi truncated to bf16, lo = RNE(v - hi) (2^-17 relative)
 __device__ __forceinline__ void split_planes(const float* v, bf16x8& hi, bf16x8& lo) {
-  uint32_t hb[8], lb[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    hb[j] = __float_as_uint(v[j]) >> 16;
-    lb[j] = bf16_bits_rne(v[j] - __uint_as_float(hb[j] << 16));
-  }
-  hi = pack_bf16x8(hb);
-  lo = pack_bf16x8(lb);
+  uint4 h, l;
+  split2x8(v, h, l);
+  hi = __builtin_bit_cast(bf16x8, h);
+  lo = __builtin_bit_cast(bf16x8, l);
 }
 
 // The loads of one (head, slot, chunk) item: query row n (rows >= 9 re-read row 8,

@@ -63,11 +63,19 @@ template <typename S>
 __device__ __forceinline__ S from_f(float f);
 template <>
 __device__ __forceinline__ float from_f<float>(float f) { return f; }
-// round to nearest even; NaN stays NaN (branch-free)
-__device__ __forceinline__ uint32_t bf16_bits_rne(float f) {
-  const uint32_t u = __float_as_uint(f);
-  const uint32_t rne = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-  return (u & 0x7fffffffu) > 0x7f800000u ? ((u >> 16) | 0x40u) : rne;
+// Round to nearest even on the conversion instruction (NaN stays NaN): one
+// instruction, and two values at once in pack2_bf16.  The integer form of the same
+// rounding took eight per value, half of an attention step's instructions (large-v3
+// step: 96 slots 14.05 -> 13.68 ms, 16 slots 5.16 -> 5.09; encoder 6.79 -> 6.63).
+typedef __bf16 bf16v2 __attribute__((ext_vector_type(2)));
+typedef float floatv2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack2_bf16(float a, float b) {  // a in the low half
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatv2{a, b}, bf16v2));
+}
+__device__ __forceinline__ uint32_t bf16_bits_rne(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+// The upper halves of a and b (bf16 by truncation), a in the low half.
+__device__ __forceinline__ uint32_t pack2_hi(float a, float b) {
+  return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
 }
 template <>
 __device__ __forceinline__ bf16 from_f<bf16>(float f) {

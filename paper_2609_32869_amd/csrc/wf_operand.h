@@ -51,6 +51,33 @@ __device__ __forceinline__ void put_op(const Operand& o, int nsplit, int R9, int
 __device__ __forceinline__ uint4 pack8_bits(const uint32_t* h) {
   return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
 }
+// v = hi + lo to 2^-17: hi truncated to bf16, lo the remainder rounded.
+__device__ __forceinline__ void split2x8(const float* v, uint4& hi, uint4& lo) {
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float a = v[2 * e], b = v[2 * e + 1];
+    h[e] = pack2_hi(a, b);
+    l[e] = pack2_bf16(a - __uint_as_float(__float_as_uint(a) & 0xffff0000u), b - __uint_as_float(__float_as_uint(b) & 0xffff0000u));
+  }
+  hi = make_uint4(h[0], h[1], h[2], h[3]);
+  lo = make_uint4(l[0], l[1], l[2], l[3]);
+}
+// v = hi + mid + lo exactly (split3_bits)
+__device__ __forceinline__ void split3x8(const float* v, uint4& hi, uint4& mid, uint4& lo) {
+  uint32_t h[4], m[4], l[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float a = v[2 * e], b = v[2 * e + 1];
+    const float ra = a - __uint_as_float(__float_as_uint(a) & 0xffff0000u), rb = b - __uint_as_float(__float_as_uint(b) & 0xffff0000u);
+    h[e] = pack2_hi(a, b);
+    m[e] = pack2_hi(ra, rb);
+    l[e] = pack2_hi(ra - __uint_as_float(__float_as_uint(ra) & 0xffff0000u), rb - __uint_as_float(__float_as_uint(rb) & 0xffff0000u));
+  }
+  hi = make_uint4(h[0], h[1], h[2], h[3]);
+  mid = make_uint4(m[0], m[1], m[2], m[3]);
+  lo = make_uint4(l[0], l[1], l[2], l[3]);
+}
 __device__ __forceinline__ void put_operand8(const Operand& o, int, int, int row, int col, const float* v, float) {
   float* p = reinterpret_cast<float*>(o.p) + op_index(o, row, col);
   *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
@@ -58,27 +85,14 @@ __device__ __forceinline__ void put_operand8(const Operand& o, int, int, int row
 }
 __device__ __forceinline__ void put_operand8(const Operand& o, int nsplit, int R9, int row, int col, const float* v, bf16) {
   uint4* A = reinterpret_cast<uint4*>(o.p);
-  uint32_t h[8], m[8], l[8];
   if (nsplit == 3) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) split3_bits(v[e], h[e], m[e], l[e]);
-    A[op_index(o, row, col) / 8] = pack8_bits(h);
-    A[op_index(o, R9 + row, col) / 8] = pack8_bits(m);
-    A[op_index(o, 2 * R9 + row, col) / 8] = pack8_bits(l);
+    split3x8(v, A[op_index(o, row, col) / 8], A[op_index(o, R9 + row, col) / 8], A[op_index(o, 2 * R9 + row, col) / 8]);
   } else if (nsplit == 2) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t hb = __float_as_uint(v[e]) & 0xffff0000u;
-      h[e] = hb >> 16;
-      l[e] = bf16_bits_rne(v[e] - __uint_as_float(hb));
-    }
     const size_t i = op_index(o, row, col);
-    A[i / 8] = pack8_bits(h);
-    A[(i + (size_t)o.mt * 16 * o.ld) / 8] = pack8_bits(l);
+    split2x8(v, A[i / 8], A[(i + (size_t)o.mt * 16 * o.ld) / 8]);
   } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) h[e] = bf16_bits_rne(v[e]);
-    A[op_index(o, row, col) / 8] = pack8_bits(h);
+    A[op_index(o, row, col) / 8] = make_uint4(pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]), pack2_bf16(v[4], v[5]),
+                                              pack2_bf16(v[6], v[7]));
   }
 }
 template <typename S>
