@@ -266,6 +266,17 @@ int compute_layout(const wf_config& c, Layout& L) {
   L.xpart = region(std::max((size_t)kXrMaxPartials, xrec) * kXrPart * 4);
   L.lncd = region(L.nsplit_op == 3 ? cw * 4 : 0);
   L.stamps = region((size_t)kStampSlots * kStampWords * 8);
+  // prompt pass over many rows: every prompt of a call up to kPreMaxRows rows, the
+  // operands as bf16 planes
+  L.pre_rows = c.dtype == WF_BF16 ? (int)std::min(B * (size_t)c.n_ctx, (size_t)kPreMaxRows) : 0;
+  const size_t PR = L.pre_rows, pb = (size_t)L.nsplit_op * 2;
+  L.pre_h = region(PR * d * 4);
+  L.pre_q = region(PR * d * 4);
+  L.pre_a = region(PR * d * pb);
+  L.pre_f = region(PR * F * pb);
+  L.pre_tap = region(PR * c.n_tap * d * pb);
+  L.pre_part = region(kPreMaxSplit * PR * d * 4);
+  L.pre_info = region(PR ? B * L.pages_per_slot * (sizeof(PrePart) + sizeof(int2)) : 0);
   L.total = o;
   return WF_OK;
 }
@@ -273,6 +284,46 @@ int compute_layout(const wf_config& c, Layout& L) {
 }  // namespace wf
 
 namespace {
+
+// A prompt call cut into parts of 16 positions, passes of at most pre_rows rows and
+// attention groups of up to nq consecutive parts of one slot (indices within the pass).
+struct PrePass {
+  int part0, nparts, group0, ngroups;
+};
+struct PrePlan {
+  std::vector<PrePart> parts;  // empty: the nine-row passes
+  std::vector<int2> groups;
+  std::vector<PrePass> passes;
+  int nq = 1;
+};
+
+// Prompts of more nine-row passes than this take the many-row pass, which costs about
+// 4 ms for up to 64 rows at large-v3 shapes: with one slot a nine-row pass takes 1.4 ms
+// (18 tokens 2.9 against 4.0 ms, 27 tokens 4.3 against 3.9), with several 3.4-4.6.
+int pre_min_passes(const Layout& L) { return L.nsplit_op == 3 ? 2 : 1; }
+PrePlan pre_plan(const Handle* h, int slot0, int n, const int32_t* lens, int max_len) {
+  PrePlan pl;
+  const Layout& L = h->lay;
+  if (L.pre_rows == 0 || (max_len + kRows - 1) / kRows <= pre_min_passes(L)) return pl;
+  for (int s = 0; s < n; ++s)
+    for (int p = 0; p < lens[s]; p += kPrePart)
+      pl.parts.push_back({slot0 + s, p, std::min(kPrePart, lens[s] - p), p + kPrePart >= lens[s]});
+  const int np = (int)pl.parts.size(), cap = L.pre_rows / kPrePart;
+  const int npass = (np + cap - 1) / cap, per = (np + npass - 1) / npass;  // even passes
+  pl.nq = per * h->cfg.n_head > kPreCus ? 2 : 1;  // more than one round of blocks: two parts a block
+  for (int p0 = 0; p0 < np; p0 += per) {
+    PrePass ps{p0, std::min(per, np - p0), (int)pl.groups.size(), 0};
+    for (int i = 0; i < ps.nparts;) {
+      int k = 1;
+      while (k < pl.nq && i + k < ps.nparts && pl.parts[p0 + i + k].slot == pl.parts[p0 + i].slot) ++k;
+      pl.groups.push_back(int2{i, k});
+      i += k;
+    }
+    ps.ngroups = (int)pl.groups.size() - ps.group0;
+    pl.passes.push_back(ps);
+  }
+  return pl;
+}
 
 template <typename S>
 struct Runner {
@@ -859,7 +910,100 @@ struct Runner {
     }
   }
 
-  void prefill(int slot0, int n, const int* tokens, int pmax, int max_len, int* first) {
+  // The prompt's rows all at once (k_pre.hip).  info: the call's parts and groups in
+  // host memory, which outlive the stream's work.
+  void prefill_wide(int slot0, int n, const int* tokens, int pmax, const PrePlan& plan) {
+    const int d = c.d_model, F = c.d_ff, planes = L.nsplit_op, mt = L.pre_rows / kPrePart;
+    const int np = (int)plan.parts.size();
+    char* info = h->at<char>(L.pre_info);
+    PrePart* parts = reinterpret_cast<PrePart*>(info);
+    int2* groups = reinterpret_cast<int2*>(info + (size_t)c.max_batch * L.pages_per_slot * sizeof(PrePart));
+    (void)hipMemcpyAsync(parts, plan.parts.data(), np * sizeof(PrePart), hipMemcpyHostToDevice, st);
+    (void)hipMemcpyAsync(groups, plan.groups.data(), plan.groups.size() * sizeof(int2), hipMemcpyHostToDevice, st);
+    float *h_ = F32(L.pre_h), *q = F32(L.pre_q), *part = F32(L.pre_part);
+    bf16 *A = h->at<bf16>(L.pre_a), *Af = h->at<bf16>(L.pre_f), *Atap = h->at<bf16>(L.pre_tap);
+    const int* ptab = I32(L.page_table);
+    auto Wb = [&](size_t off) { return reinterpret_cast<const bf16*>(W(off)); };
+    for (const PrePass& ps : plan.passes) {
+      const int rows = ps.nparts * kPrePart;
+      PreArgs pa{};
+      pa.parts = parts + ps.part0; pa.tokens = tokens; pa.emb = W(L.tok_emb); pa.emb_kind = wk(true); pa.pos = W(L.pos_emb);
+      pa.h = h_; pa.slot0 = slot0; pa.pmax = pmax; pa.d = d; pa.n_vocab = c.n_vocab;
+      pre_begin(pa, ps.nparts, st);
+      // y = A W^T in the given epilogue; returns the k-splits of PRE_PART
+      auto product = [&](int epi, const bf16* a, size_t w, size_t b, int N, int K, float* y, int ldy, bf16* aout,
+                         S* cache = nullptr, bool wide = false) {
+        PreGemmArgs g{};
+        g.a = a; g.mt = mt; g.w = Wb(w); g.wkind = wk(wide); g.bias = Wb(b); g.M = rows; g.N = N; g.K = K;
+        g.y = y; g.ldy = ldy; g.pstride = (size_t)L.pre_rows * d; g.aout = aout;
+        g.parts = pa.parts; g.page_table = ptab; g.pages_per_slot = L.pages_per_slot; g.d = d; g.n_head = c.n_head;
+        g.cache = cache; g.kv_stride = kv_stride();
+        return pre_gemm(epi, g, planes, st);
+      };
+      // h += partial sums + bias, the tap of a tapped block, and the next LayerNorm
+      auto reduce = [&](int nparts, size_t b, size_t lg, size_t lb, bool ln, int tap = -1, bool fresh = false) {
+        PreLnArgs r{};
+        r.h = h_; r.part = part; r.pstride = (size_t)L.pre_rows * d; r.nparts = nparts; r.fresh = fresh ? 1 : 0;
+        r.bias = Wb(b); r.tap = Atap; r.tapcol = tap >= 0 ? tap * d : -1; r.tapld = c.n_tap * d;
+        r.g = ln ? Wb(lg) : nullptr; r.b = Wb(lb); r.out = A; r.mt = mt; r.d = d;
+        pre_rln(r, planes, rows, st);
+      };
+      auto attend = [&](bool cross, const S* k, const S* v) {
+        PreAttnArgs t{};
+        t.q = q; t.ldq = d; t.k = k; t.v = v; t.parts = pa.parts; t.groups = groups + ps.group0; t.page_table = ptab;
+        t.pages_per_slot = L.pages_per_slot; t.n_frames = c.n_frames; t.vt_frames = vt_frames(); t.d = d; t.n_head = c.n_head;
+        t.out = A; t.mt = mt;
+        pre_attn(t, cross, planes, plan.nq, ps.ngroups, st);
+      };
+      reduce(0, 0, L.tb[0].ln1_g, L.tb[0].ln1_b, true);
+      for (int l = 0; l < c.n_layer; ++l) {
+        const BlockW& b = L.tb[l];
+        int tap = -1;
+        for (int i = 0; i < c.n_tap; ++i)
+          if (c.taps[i] == l) tap = i;
+        product(PRE_QKV, A, b.w_qkv, b.b_qkv, 3 * d, d, q, d, nullptr, skv_layer(l));
+        attend(false, skv_layer(l), skv_layer(l) + kv_stride());
+        int ks = product(PRE_PART, A, b.w_o, b.b_o, d, d, part, d, nullptr);
+        reduce(ks, b.b_o, b.ln2_g, b.ln2_b, true);
+        product(PRE_STORE, A, b.w_q2, b.b_q2, d, d, q, d, nullptr);
+        attend(true, xkv_layer(l), nullptr);
+        ks = product(PRE_PART, A, b.w_o2, b.b_o2, d, d, part, d, nullptr);
+        reduce(ks, b.b_o2, b.ln3_g, b.ln3_b, true);
+        product(PRE_GELU, A, b.w_fc1, b.b_fc1, F, d, nullptr, 0, Af, nullptr, true);
+        ks = product(PRE_PART, Af, b.w_fc2, b.b_fc2, d, F, part, d, nullptr);
+        const bool more = l + 1 < c.n_layer;
+        reduce(ks, b.b_fc2, more ? L.tb[l + 1].ln1_g : 0, more ? L.tb[l + 1].ln1_b : 0, more, tap);
+      }
+      pre_last(pa, ps.nparts, F32(L.lasth), st);
+      if (c.draft_flags & WF_DRAFT_NO_HISTORY) continue;
+      // drafter history: the taps' projection in place of the residual rows, then
+      // every block's LayerNorm, k | v product and cache rows
+      const int ks = product(PRE_PART, Atap, L.hproj_w, L.hproj_b, d, c.n_tap * d, part, d, nullptr);
+      for (int dl = 0; dl < c.n_draft_layer; ++dl) {
+        const BlockW& b = L.db[dl];
+        reduce(dl == 0 ? ks : 0, L.hproj_b, b.ln1_g, b.ln1_b, true, -1, true);
+        product(PRE_STORE, A, b.w_qkv + (size_t)d * d, b.b_qkv + d, 2 * d, d, part, 2 * d, nullptr);
+        PreHistArgs ha{};
+        ha.kv = part; ha.parts = pa.parts; ha.kcache = hkv(dl, 0); ha.vcache = hkv(dl, 1); ha.rope = F32(L.rope);
+        ha.use_rope = !(c.draft_flags & WF_DRAFT_ABS_POS); ha.d = d; ha.n_head = c.n_head; ha.n_ctx = c.n_ctx;
+        pre_hist(ha, ps.nparts, st);
+      }
+    }
+  }
+
+  void prefill(int slot0, int n, const int* tokens, int pmax, int max_len, const PrePlan& plan, int* first) {
+    if (!plan.parts.empty()) {
+      if constexpr (std::is_same<S, bf16>::value) prefill_wide(slot0, n, tokens, pmax, plan);
+    } else {
+      prefill_chunks(slot0, n, tokens, pmax, max_len);
+    }
+    ln_ready = false;  // the final LayerNorm applies to the saved last rows, not to h
+    head(slot0, n, F32(L.lasth), L.lnf_g, L.lnf_b, nullptr, nullptr, nullptr, RNG_PREFILL);
+    prefill_finish(I32(L.state), I32(L.g), slot0, n, c.eos_id, c.n_ctx, first, st);
+  }
+
+  // Nine positions of every prompt per pass, through the step's kernels.
+  void prefill_chunks(int slot0, int n, const int* tokens, int pmax, int max_len) {
     const int nchunks = (max_len + kRows - 1) / kRows;
     BeginArgs ba{};
     ba.state = I32(L.state); ba.draft = tokens; ba.tok = I32(L.tok); ba.emb = W(L.tok_emb); ba.emb_kind = wk(true); ba.pos = W(L.pos_emb);
@@ -874,9 +1018,6 @@ struct Runner {
       save_last(F32(L.h), F32(L.lasth), I32(L.state), slot0, n, c.d_model, ch, st);
       history_apply(slot0, n);
     }
-    ln_ready = false;  // the final LayerNorm applies to the saved last rows, not to h
-    head(slot0, n, F32(L.lasth), L.lnf_g, L.lnf_b, nullptr, nullptr, nullptr, RNG_PREFILL);
-    prefill_finish(I32(L.state), I32(L.g), slot0, n, c.eos_id, c.n_ctx, first, st);
   }
 };
 
@@ -1126,9 +1267,10 @@ int wf_prefill(wf_handle* hh, int slot0, int n, const int32_t* tokens, int pmax,
   }
   HIPCK(h, hipMemcpyAsync(h->at<int>(h->lay.state) + (size_t)slot0 * kStateInts, init.data(), init.size() * 4,
                           hipMemcpyHostToDevice, st));
+  const PrePlan plan = pre_plan(h, slot0, n, lens, max_len);
   int r = dispatch(h, st, [&](auto* tag) {
     using S = std::remove_pointer_t<decltype(tag)>;
-    Runner<S>(h, st).prefill(slot0, n, tokens, pmax, max_len, first);
+    Runner<S>(h, st).prefill(slot0, n, tokens, pmax, max_len, plan, first);
   });
   if (r) return r;
   HIPCK(h, hipStreamSynchronize(st));

@@ -33,6 +33,10 @@ struct Layout {
   size_t xpart;   // chunked cross-attention: partial records
   size_t lncd;    // LayerNorm column sums of the folded products (batch 1, bf16)
   size_t stamps;  // launch timing slots (profiling)
+  // prompt pass over many rows (bf16): residual rows, queries, operands, partial
+  // sums and the call's parts
+  size_t pre_h, pre_q, pre_a, pre_f, pre_tap, pre_part, pre_info;
+  int pre_rows;   // rows of one pass (0: fp32 storage)
   size_t total;
   // element offsets inside the weight region
   size_t tok_emb, pos_emb, lnf_g, lnf_b, hproj_w, hproj_b, mask, dlnf_g, dlnf_b;

@@ -358,6 +358,84 @@ struct EncAttnArgs {
 };
 void enc_attention(const EncAttnArgs& a, int n_head, hipStream_t st);
 
+// Prompt pass over many rows (k_pre.hip, bf16 storage): parts of 16 positions, each
+// one cache page; row part * 16 + i of the pass is position pos0 + i of the slot.
+constexpr int kPrePart = 16;
+static_assert(kPrePart == kPage, "a part's keys and values fill one cache page");
+constexpr int kPreMaxRows = 2048;  // rows of one pass (more parts: several passes)
+constexpr int kPreMaxSplit = 4;    // k-splits of a product that leaves partial sums
+constexpr size_t kPreXcdRowBytes = (size_t)5 << 19;  // operand bytes one XCD's blocks share at most (L2: 4 MB)
+constexpr int kPreCus = 256;       // compute units: blocks of one round
+struct PrePart {
+  int slot, pos0, nv, last;  // nv valid rows; last: the prompt's last part
+};
+struct PreArgs {
+  const PrePart* parts;
+  const int* tokens;  // [n][pmax]
+  const void* emb;
+  int emb_kind;
+  const void* pos;
+  float* h;
+  int slot0, pmax, d, n_vocab;
+};
+struct PreLnArgs {
+  float* h;           // rows [rows][d]
+  const float* part;  // [nparts][rows][d] partial sums (nparts 0: none)
+  size_t pstride;
+  int nparts, fresh;  // fresh: the rows start at the partial sums instead of adding them
+  const bf16* bias;
+  bf16* tap;          // tap operand (row length tapld, column offset tapcol) when tapcol >= 0
+  int tapcol, tapld;
+  const bf16* g;      // LayerNorm into `out`, or null
+  const bf16* b;
+  bf16* out;
+  int mt, d;          // 16-row tiles held by the operand buffers
+};
+enum { PRE_STORE = 0, PRE_PART = 1, PRE_GELU = 2, PRE_QKV = 3 };
+struct PreGemmArgs {
+  const bf16* a;      // operand planes of K columns
+  int mt;             // 16-row tiles held by operand buffers
+  const bf16* w;
+  int wkind;
+  const bf16* bias;
+  int M, N, K;
+  float* y;           // STORE rows, PART partial sums, QKV queries
+  int ldy;
+  size_t pstride;
+  bf16* aout;         // GELU: operand planes of N columns
+  const PrePart* parts;
+  const int* page_table;
+  int pages_per_slot, d, n_head;
+  void* cache;
+  size_t kv_stride;
+};
+struct PreAttnArgs {
+  const float* q;
+  int ldq;
+  const void* k;      // self: key cache; cross: acoustic keys and values of the block
+  const void* v;
+  const PrePart* parts;
+  const int2* groups; // (first part, parts): consecutive parts of one slot
+  const int* page_table;
+  int pages_per_slot, n_frames, vt_frames, d, n_head;
+  bf16* out;
+  int mt;
+};
+struct PreHistArgs {
+  const float* kv;    // [rows][2d]
+  const PrePart* parts;
+  void* kcache;
+  void* vcache;
+  const float* rope;
+  int use_rope, d, n_head, n_ctx;
+};
+void pre_begin(const PreArgs& a, int nparts, hipStream_t st);
+void pre_last(const PreArgs& a, int nparts, float* lasth, hipStream_t st);
+void pre_rln(const PreLnArgs& a, int planes, int rows, hipStream_t st);
+int pre_gemm(int epi, const PreGemmArgs& a, int planes, hipStream_t st);  // k-splits used
+void pre_attn(const PreAttnArgs& a, bool cross, int planes, int nq, int ngroups, hipStream_t st);
+void pre_hist(const PreHistArgs& a, int nparts, hipStream_t st);
+
 template <typename S>
 struct Ops {
   static void ln_operand(const LnArgs& a, int rows, hipStream_t st);

@@ -1,0 +1,94 @@
+"""The many-row prompt pass (bf16 storage, prompts of more than two nine-row passes)
+against the oracle: first token, then draft and target logits of steps that read
+every key, value and drafter-history row the pass wrote.
+
+Sizes are those at which it can go wrong: prompts that end inside, at and just past a
+16-position part, the context's last position, one to many slots (three and two
+operand planes, one or two parts per attention block, several passes), 64- and
+128-column product tiles, k-splits of one, two and four, frame counts that end
+inside a 32-frame step.  Tolerances are the repository's: both sides keep their
+caches in bf16 and compute in fp32, and the bar is far above the differences seen
+(at most 8e-3) and far below those of a wrong row (0.1 and more).
+"""
+import numpy as np
+import pytest
+import torch
+
+from wf_fixtures import MICRO, make_weights, make_memory, make_prefix
+from oracle import OracleOpts, Session
+
+pytestmark = pytest.mark.gpu
+
+TOL_MICRO, TOL = 1e-3, 2e-2
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _run(cfg, lens, tol, std=0.02, check=None, steps=2):
+    from lockstep import Lockstep
+    W = make_weights(cfg, std=std)
+    prompts = [make_prefix(cfg, i, n) for i, n in enumerate(lens)]
+    ls = Lockstep(cfg, W, prompts, [cfg.n_ctx] * len(lens), tol, check=check,
+                  opts=OracleOpts(dtype=np.float32, kv_bf16=True))
+    for _ in range(steps):
+        ls.step()
+    print(f"{cfg.name} x{len(lens)}: max |dlogit| draft {ls.max_dlogit:.2e} target {ls.max_tlogit:.2e}, "
+          f"near ties {ls.near_ties}")
+    return ls
+
+
+@pytest.mark.parametrize("lens", [[19], [31], [32], [33], [64 - 9], [19, 48, 5], [32, 1, 33, 17, 55]])
+def test_part_edges(lens):
+    cfg = MICRO.with_(name="micro-bf16-pre", dtype="bf16", n_vocab=501, n_frames=45)
+    _run(cfg, lens, TOL_MICRO).close()
+
+
+@pytest.mark.parametrize("n_frames,flags", [(31, {}), (33, {"draft_history": False}), (300, {"draft_pos": "abs"}),
+                                            (300, {"draft_audio": False})])
+def test_frames_and_variants(n_frames, flags):
+    cfg = MICRO.with_(name="micro-bf16-pre", dtype="bf16", n_vocab=501, n_frames=n_frames, **flags)
+    _run(cfg, [40, 23], TOL_MICRO).close()
+
+
+def test_prompt_fills_the_context():
+    """A prompt of n_ctx - 1 tokens leaves one position: its step verifies the anchor."""
+    cfg = MICRO.with_(name="micro-bf16-pre", dtype="bf16", n_vocab=501)
+    for lens in ([63], [63, 64]):
+        ls = _run(cfg, lens, TOL_MICRO, steps=1)
+        assert ls.eng.state()[:len(lens), 4].cpu().tolist() == [1] * len(lens)
+        ls.close()
+
+
+@pytest.mark.parametrize("d_model,batch,lens", [(512, 12, (50, 64)), (512, 20, (40, 64)), (768, 40, (33, 64))])
+def test_many_slots(d_model, batch, lens):
+    """One and two parts per attention block, groups that end inside a slot, several
+    passes (40 slots of up to four parts: 2560 rows in two)."""
+    cfg = MICRO.with_(name=f"w{d_model}-pre", dtype="bf16", n_layer=2, d_model=d_model, n_head=d_model // 64,
+                      d_ff=4 * d_model, n_vocab=501, taps=(0, 1), n_ctx=64, n_frames=70)
+    ls_ = [lens[0] + (7 * i) % (lens[1] - lens[0] - 8) for i in range(batch)]
+    _run(cfg, ls_, TOL, std=0.05, check=[0, 1, batch // 2, batch - 1], steps=1).close()
+
+
+@pytest.mark.parametrize("length", [150, 230, 430])
+def test_width_1280_tiles(length):
+    """One slot at width 1280: 64 x 64 and 64 x 128 tiles of the three-plane products,
+    k-splits of one, two and four."""
+    cfg = MICRO.with_(name="w1280-pre", dtype="bf16", n_layer=2, d_model=1280, n_head=20, d_ff=5120, n_vocab=501,
+                      taps=(0, 1), n_ctx=448, n_frames=130)
+    _run(cfg, [length], TOL, steps=1).close()
+
+
+def test_refill_leaves_other_slots():
+    """A slot prefilled again in a running batch: its neighbours' caches stay theirs."""
+    cfg = MICRO.with_(name="micro-bf16-pre", dtype="bf16", n_vocab=501)
+    ls = _run(cfg, [30, 41, 25], TOL_MICRO)
+    prompt = make_prefix(cfg, 9, 37)
+    ls.eng.prefill(1, torch.from_numpy(prompt[None].copy()).cuda(), [37], [cfg.n_ctx])
+    ls.sess[1] = Session(ls.T, ls.D, make_memory(cfg, 1), prompt, cfg.n_ctx)
+    for _ in range(2):
+        ls.step()
+    ls.close()
