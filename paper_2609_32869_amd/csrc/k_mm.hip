@@ -5,8 +5,8 @@
 // decoder block for a new request (Appendix A.5) and the products of the
 // audio encoder.
 //
-// Tiling: BMT x 128 output tiles (BMT = 128, or 64 when 128-row tiles would
-// leave CUs idle), k in steps of 64, 256 threads = 2 x 2 waves of BMT/2 x 64
+// Tiling: BMT x 128 output tiles (BMT = 128 or 64; 256 in k_mmw below), k in steps
+// of 64, 256 threads = 2 x 2 waves of BMT/2 x 64
 // (BMT/64 x 2 tiles of v_mfma_f32_32x32x16_bf16).  A and B tiles are copied
 // straight from memory into LDS stages (global_load_lds_dwordx4): two stages one
 // k-step ahead for 128-row tiles (two blocks share a CU), four stages three
@@ -51,17 +51,23 @@ static_assert(kStageU4 >= 2 * kChunksB, "stage holds a 128-row k-step");
 __shared__ uint4 g_mm0[kStageU4], g_mm1[kStageU4], g_mm2[kStageU4], g_mm3[kStageU4];
 
 template <int EP, int BM, int NS>
-__global__ void __launch_bounds__(NT) k_mm(MmArgs a) {
+__global__ void __launch_bounds__(NT) k_mm(MmArgs a, int nmb, int nnb, int rs) {
   static_assert(NS == 2 || NS == 4, "two or four stages");
   constexpr int kChunksA = BM * BK / 8, JA = kChunksA / NT, MI = BM / 64;
   // copies per wave and k-step: JA of A, 4 of B; a step waits until at most the
   // NS - 2 later k-steps' copies are outstanding (and its earlier LDS reads are done)
   constexpr int kCopies = JA + 4, kVm = (NS - 2) * kCopies;
   constexpr int kWait = (kVm & 15) | ((kVm >> 4) << 14) | (7 << 4) | (0 << 8);
+  // XCD x (block % 8) takes row part x % rs of rs and column part x / rs of 8 / rs, row
+  // blocks fastest, so the blocks that share an L2 share their rows and columns
+  const int x8 = blockIdx.x & 7, bi = blockIdx.x >> 3;
+  const int nrh = (nmb + rs - 1) / rs, ncq = (nnb * rs + 7) / 8;
+  const int mbk = (x8 % rs) * nrh + bi % nrh, nbk = (x8 / rs) * ncq + bi / nrh;
+  if (mbk >= nmb || bi / nrh >= ncq || nbk >= nnb) return;
   const int z = blockIdx.z;
   const bf16* A = a.A + (size_t)z * a.sA;
   const bf16* B = a.B + (size_t)z * a.sB;
-  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+  const int m0 = mbk * BM, n0 = nbk * BN;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int wm = w >> 1, wn = w & 1;
   const int nk = a.K / BK, nbB = a.nb > 0 ? a.nb : a.N;
@@ -241,6 +247,186 @@ __global__ void __launch_bounds__(NT) k_mm(MmArgs a) {
   }
 }
 
+// The same products on 256 x 128 tiles, eight waves of 64 x 64 (two per SIMD), for
+// launches whose larger tiles still cover the chip: three LDS stages, two k-steps
+// ahead.  Within a k-step the fragment reads of the next 16-wide substep and the
+// copies of a later k-step are issued between the multiplications, since a wave
+// stalls while its copies are taken up.  The finished 32 x 32 tiles are turned
+// around in each wave's own LDS.  6144 rows, K = 5120, N = 1280: 1060 TFLOP/s (a large
+// library product reaches 1190 on this card); 1500 rows, N = 2560, 34 matrices 0.40 ms
+// against 0.47 on the 128-row tiles and 0.53 before those had their XCD order.  256 x
+// 256 tiles in two stages: 0.47 ms.
+template <int EP>
+__global__ void __launch_bounds__(512, 2) k_mmw(MmArgs a, int nmb, int nnb, int rs) {
+  constexpr int BM = 256, WC = 2, WR = 4, MI = 2, NJ = 2, NS = 3;
+  constexpr int kA = BM * BK / 8, JA = kA / 512, JB = kChunksB / 512, CPW = JA + JB;
+  constexpr int kVm = (NS - 2) * CPW;
+  constexpr int kWait = (kVm & 15) | ((kVm >> 4) << 14) | (7 << 4) | (0 << 8);
+  constexpr int kStage = kA + kChunksB;
+  __shared__ uint4 g_mw0[kStage], g_mw1[kStage], g_mw2[kStage];
+  const int x8 = blockIdx.x & 7, bi = blockIdx.x >> 3;
+  const int nrh = (nmb + rs - 1) / rs, ncq = (nnb * rs + 7) / 8;
+  const int mbk = (x8 % rs) * nrh + bi % nrh, nbk = (x8 / rs) * ncq + bi / nrh;
+  if (mbk >= nmb || bi / nrh >= ncq || nbk >= nnb) return;
+  const int z = blockIdx.z;
+  const bf16* A = a.A + (size_t)z * a.sA;
+  const bf16* B = a.B + (size_t)z * a.sB;
+  const int m0 = mbk * BM, n0 = nbk * BN;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int wm = w / WC, wn = w % WC, lr = lane & 31, lk = lane >> 5;
+  const int nk = a.K / BK, nbB = a.nb > 0 ? a.nb : a.N;
+  // copy sources as in k_mm: slot s holds row s / 8, chunk (s % 8) ^ (row & 7)
+  const bf16* src[CPW];
+#pragma unroll
+  for (int j = 0; j < CPW; ++j) {
+    const bool isA = j < JA;
+    const int slot = (w * (isA ? JA : JB) + (isA ? j : j - JA)) * 64 + lane, row = slot >> 3, ch = (slot & 7) ^ (row & 7);
+    src[j] = isA ? A + (size_t)min(m0 + row, a.M - 1) * a.lda + 8 * ch : B + (size_t)min(n0 + row, nbB - 1) * a.ldb + 8 * ch;
+  }
+  auto copy1 = [&](int j, int k0, uint4* stage) {
+    __builtin_amdgcn_global_load_lds((const void*)(src[j] + k0),
+                                     (lds_void*)&stage[j < JA ? (w * JA + j) * 64 : kA + (w * JB + j - JA) * 64], 16, 0, 0);
+  };
+  floatx16 acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  bf16x8 fr[2][MI + NJ];
+  auto read1 = [&](const uint4* st, int s, int r, bf16x8* f) {  // fragment r of substep s: rows, then columns
+    const int q = 2 * s + lk;
+    if (r < MI) {
+      const int row = (wm * MI + r) * 32 + lr;
+      f[r] = __builtin_bit_cast(bf16x8, st[row * 8 + (q ^ (row & 7))]);
+    } else {
+      const int row = (wn * NJ + r - MI) * 32 + lr;
+      f[r] = __builtin_bit_cast(bf16x8, st[kA + row * 8 + (q ^ (row & 7))]);
+    }
+  };
+  constexpr int NM = MI * NJ, NR = MI + NJ;
+  auto kstep = [&](int kt, const uint4* cur, uint4* nxt) {
+    __builtin_amdgcn_s_waitcnt(kWait);
+    __builtin_amdgcn_s_barrier();
+    const int k0 = min(kt + NS - 1, nk - 1) * BK;  // every step issues its copies, so the wait count stays exact
+#pragma unroll
+    for (int r = 0; r < NR; ++r) read1(cur, 0, r, fr[0]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        acc[m / NJ][m % NJ] =
+            __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[s & 1][m / NJ], fr[s & 1][MI + m % NJ], acc[m / NJ][m % NJ], 0, 0, 0);
+        if (s < 3) {
+#pragma unroll
+          for (int r = m * NR / NM; r < (m + 1) * NR / NM; ++r) read1(cur, s + 1, r, fr[(s + 1) & 1]);
+        }
+#pragma unroll
+        for (int j = (s * NM + m) * CPW / (4 * NM); j < (s * NM + m + 1) * CPW / (4 * NM); ++j) copy1(j, k0, nxt);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  };
+  auto stage = [&](int i) -> uint4* { return i == 0 ? g_mw0 : i == 1 ? g_mw1 : g_mw2; };
+#pragma unroll
+  for (int i = 0; i < NS - 1; ++i)
+#pragma unroll
+    for (int j = 0; j < CPW; ++j) copy1(j, min(i, nk - 1) * BK, stage(i));
+  int kt = 0;
+  for (; kt + NS <= nk; kt += NS) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) kstep(kt + i, stage(i), stage((i + NS - 1) % NS));
+  }
+#pragma unroll
+  for (int i = 0; i < NS - 1; ++i)
+    if (kt + i < nk) kstep(kt + i, stage(i), stage((i + NS - 1) % NS));
+  __builtin_amdgcn_s_waitcnt((0 & 15) | (7 << 4) | (15 << 8));  // every copy has landed
+  __syncthreads();
+
+  // accumulator v of a 32 x 32 tile: row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32
+  float* tr = reinterpret_cast<float*>(g_mw0) + w * 16 * 33;
+  const bf16* bias = a.bias ? a.bias + (size_t)z * a.sBias : nullptr;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int nt = n0 + (wn * NJ + j) * 32, nc = nt + lr;
+    if (nt >= a.N) continue;  // uniform
+    const float bv = bias ? to_f(bias[min(nc, a.N - 1)]) : 0.f;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int mt = m0 + (wm * MI + i) * 32;
+      const int nrow = EP == MM_XKV ? a.d : EP == MM_QKV_ENC ? 2 * a.d : 1 << 30;
+      floatx16 c = acc[i][j];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        c[v] = c[v] * a.scale + bv;
+        if (EP == MM_BF16_GELU || EP == MM_GELU_ADD_F32) c[v] = gelu_erf(c[v]);
+      }
+      if (EP == MM_F32 || EP == MM_RESID || EP == MM_GELU_ADD_F32) {
+        float* out = reinterpret_cast<float*>(a.out) + (size_t)z * a.sO + nc;
+        if (nc < a.N) {
+          float o[16];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {  // every load first (rows past the matrix re-read its last one)
+            const int f = min(mt + 8 * (v >> 2) + 4 * lk + (v & 3), a.M - 1);
+            o[v] = EP == MM_RESID ? out[(size_t)f * a.ldo] : EP == MM_GELU_ADD_F32 ? a.add[(size_t)f * a.ldadd + nc] : 0.f;
+          }
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const int f = mt + 8 * (v >> 2) + 4 * lk + (v & 3);
+            if (f < a.M) out[(size_t)f * a.ldo] = c[v] + o[v];
+          }
+        }
+      } else if (nt < nrow) {
+        // bf16 rows: half tiles turned around in the wave's LDS, 8 columns per lane
+        bf16* out = reinterpret_cast<bf16*>(a.out) + (size_t)z * a.sO;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+#pragma unroll
+          for (int v = 0; v < 8; ++v) tr[(8 * (v >> 2) + 4 * lk + (v & 3)) * 33 + lr] = c[8 * half + v];
+          __builtin_amdgcn_wave_barrier();
+          float o[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[e] = tr[(lane >> 2) * 33 + 8 * (lane & 3) + e];
+          __builtin_amdgcn_wave_barrier();
+          const int f = mt + 16 * half + (lane >> 2), n = nt + 8 * (lane & 3);
+          if (f < a.M && n < a.N) {
+            if (EP == MM_XKV)
+              *reinterpret_cast<uint4*>(out + ((size_t)(n >> 6) * a.M + f) * kHeadDim + (n & 63)) = pack8(o);
+            else
+              *reinterpret_cast<uint4*>(out + (size_t)f * a.ldo + n) = pack8(o);
+          }
+        }
+      } else {
+        // transposed values, zero past the last frame: eight consecutive frames per lane
+        const int col = nc - nrow, head = col >> 6, dim = col & 63;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          const int f = mt + 16 * half + 8 * lk;
+          uint32_t p[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int f0 = mt + 16 * half + 8 * (e >> 1) + 4 * lk + 2 * (e & 1);
+            p[e] = pack2_bf16(f0 < a.M ? c[8 * half + 2 * e] : 0.f, f0 + 1 < a.M ? c[8 * half + 2 * e + 1] : 0.f);
+          }
+          const auto x = __builtin_amdgcn_permlane32_swap(p[0], p[2], false, false);
+          const auto y = __builtin_amdgcn_permlane32_swap(p[1], p[3], false, false);
+          if (f >= a.vt_frames) continue;
+          const uint4 pk = make_uint4(x[0], y[0], x[1], y[1]);
+          if (EP == MM_XKV) {
+            bf16* vt = reinterpret_cast<bf16*>(a.out) + (size_t)z * a.sO + (size_t)a.n_head * a.M * kHeadDim +
+                       (size_t)head * kHeadDim * a.vt_frames;
+            *reinterpret_cast<uint4*>(vt + vt_index(dim, f)) = pk;
+          } else {
+            bf16* vt = reinterpret_cast<bf16*>(a.out2) + (size_t)z * a.sO2;
+            *reinterpret_cast<uint4*>(vt + ((size_t)head * kHeadDim + dim) * a.vt_frames + f) = pk;
+          }
+        }
+      }
+    }
+  }
+}
+
 // Shapes the kernel assumes: K a multiple of 64, N a multiple of 8, 16-byte
 // aligned rows (lda, ldb, ldo multiples of 8), and for the transposed epilogues
 // head width 64 with the value columns after the row-major ones.
@@ -258,29 +444,73 @@ int mm_check(const MmArgs& a, int ep) {
   return 0;
 }
 
+namespace {
+// Blocks of a launch over the XCDs: row part x % rs of rs, column part x / rs of 8 / rs.
+// The split with the fewest rounds of blocks per XCD (32 CUs of `occ` blocks), then
+// the one whose blocks share the fewest rows and columns: 6144 rows, K = 5120, N =
+// 1280 on 256 x 128 tiles 148, 137 and 76 us with 1, 2 and 4 row parts (48, 36 and 30
+// blocks per XCD).
+struct XcdSplit {
+  int nmb, nnb, rs;
+  long long rounds;
+};
+XcdSplit xcd_split(int rows, int cols, int bm, int bn, int occ, int batch) {
+  XcdSplit best{(rows + bm - 1) / bm, (cols + bn - 1) / bn, 1, 0};
+  long long least = 0;
+  for (int rs = 1; rs <= 8; rs *= 2) {
+    const int nrh = (best.nmb + rs - 1) / rs, ncq = (best.nnb * rs + 7) / 8;
+    const long long rounds = ((long long)nrh * ncq * batch + 32 * occ - 1) / (32 * occ), share = (long long)nrh * bm + (long long)ncq * bn;
+    if (rs == 1 || rounds < best.rounds || (rounds == best.rounds && share < least)) {
+      best.rounds = rounds;
+      best.rs = rs;
+      least = share;
+    }
+  }
+  return best;
+}
+dim3 xcd_grid(const XcdSplit& x, int batch) {
+  return dim3(8u * ((x.nmb + x.rs - 1) / x.rs) * ((x.nnb * x.rs + 7) / 8), 1, batch);
+}
+}  // namespace
+
 template <int BM, int NS>
-static void mm_launch(const MmArgs& a, int ep, int batch, hipStream_t st) {
-  const dim3 grid((std::max(a.M, (ep == MM_XKV || ep == MM_QKV_ENC) ? a.vt_frames : a.M) + BM - 1) / BM,
-                  (a.N + BN - 1) / BN, batch);
+static void mm_launch(const MmArgs& a, int ep, const XcdSplit& x, int batch, hipStream_t st) {
+  const dim3 grid = xcd_grid(x, batch);
   switch (ep) {
-    case MM_F32: k_mm<MM_F32, BM, NS><<<grid, NT, 0, st>>>(a); break;
-    case MM_BF16: k_mm<MM_BF16, BM, NS><<<grid, NT, 0, st>>>(a); break;
-    case MM_BF16_GELU: k_mm<MM_BF16_GELU, BM, NS><<<grid, NT, 0, st>>>(a); break;
-    case MM_RESID: k_mm<MM_RESID, BM, NS><<<grid, NT, 0, st>>>(a); break;
-    case MM_XKV: k_mm<MM_XKV, BM, NS><<<grid, NT, 0, st>>>(a); break;
-    case MM_QKV_ENC: k_mm<MM_QKV_ENC, BM, NS><<<grid, NT, 0, st>>>(a); break;
-    case MM_GELU_ADD_F32: k_mm<MM_GELU_ADD_F32, BM, NS><<<grid, NT, 0, st>>>(a); break;
+    case MM_F32: k_mm<MM_F32, BM, NS><<<grid, NT, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+    case MM_BF16: k_mm<MM_BF16, BM, NS><<<grid, NT, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+    case MM_BF16_GELU: k_mm<MM_BF16_GELU, BM, NS><<<grid, NT, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+    case MM_RESID: k_mm<MM_RESID, BM, NS><<<grid, NT, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+    case MM_XKV: k_mm<MM_XKV, BM, NS><<<grid, NT, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+    case MM_QKV_ENC: k_mm<MM_QKV_ENC, BM, NS><<<grid, NT, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+    case MM_GELU_ADD_F32: k_mm<MM_GELU_ADD_F32, BM, NS><<<grid, NT, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+  }
+}
+static void mmw_launch(const MmArgs& a, int ep, const XcdSplit& x, int batch, hipStream_t st) {
+  const dim3 grid = xcd_grid(x, batch);
+  switch (ep) {
+    case MM_F32: k_mmw<MM_F32><<<grid, 512, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+    case MM_BF16: k_mmw<MM_BF16><<<grid, 512, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+    case MM_BF16_GELU: k_mmw<MM_BF16_GELU><<<grid, 512, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+    case MM_RESID: k_mmw<MM_RESID><<<grid, 512, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+    case MM_XKV: k_mmw<MM_XKV><<<grid, 512, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+    case MM_QKV_ENC: k_mmw<MM_QKV_ENC><<<grid, 512, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
+    case MM_GELU_ADD_F32: k_mmw<MM_GELU_ADD_F32><<<grid, 512, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
   }
 }
 
-// 128-row tiles in two stages (two blocks fit on a CU), or, when the 128-row grid
-// would cover fewer blocks than the chip has CUs (256), 64-row tiles in four
-// stages (one block per CU, three k-steps of copies in flight)
+// The tile with the least time: rounds of blocks times what a round of 1280 columns of
+// k takes (256 x 128 tiles, one block per CU, 27 us; 128 x 128 in two stages, two per
+// CU, 29; 64 x 128 in four stages, one per CU, 12).  1500 rows: 5120 columns 27, 29
+// and 54 us, 3840 columns 21, 27 and 37, 1280 columns 22, 21 and 10.
 void mm(const MmArgs& a, int ep, int batch, hipStream_t st) {
   const int rows = std::max(a.M, (ep == MM_XKV || ep == MM_QKV_ENC) ? a.vt_frames : a.M);
-  const long long blocks128 = (long long)((rows + 127) / 128) * ((a.N + BN - 1) / BN) * batch;
-  if (blocks128 < 256) mm_launch<64, 4>(a, ep, batch, st);
-  else mm_launch<128, 2>(a, ep, batch, st);
+  const XcdSplit w = xcd_split(rows, a.N, 256, BN, 1, batch), m = xcd_split(rows, a.N, 128, BN, 2, batch),
+                 n = xcd_split(rows, a.N, 64, BN, 1, batch);
+  const long long tw = 27 * w.rounds, tm = 29 * m.rounds, tn = 12 * n.rounds;
+  if (tw <= tm && tw <= tn) mmw_launch(a, ep, w, batch, st);
+  else if (tm <= tn) mm_launch<128, 2>(a, ep, m, batch, st);
+  else mm_launch<64, 4>(a, ep, n, batch, st);
 }
 
 }  // namespace wf

@@ -25,7 +25,8 @@ namespace {
 template <int P>
 __device__ __forceinline__ void put_planes8(uint4* A, size_t i, size_t plane, const float* v) {
   if constexpr (P == 3) split3x8(v, A[i], A[i + plane], A[i + 2 * plane]);
-  else split2x8(v, A[i], A[i + plane]);
+  else if constexpr (P == 2) split2x8(v, A[i], A[i + plane]);
+  else A[i] = make_uint4(pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]), pack2_bf16(v[4], v[5]), pack2_bf16(v[6], v[7]));
 }
 }  // namespace
 
@@ -69,6 +70,7 @@ template <int P>
 __global__ void __launch_bounds__(256) k_pre_rln(PreLnArgs a) {
   __shared__ float red[2][4];
   const int row = blockIdx.x, d = a.d, nch = d >> 3, c = threadIdx.x, cc = min(c, nch - 1);
+  if (a.period > 0 && row % a.period >= a.valid) return;  // padding rows stay as they are (zero)
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const bool act = c < nch, sums = a.nparts > 0, has_ln = a.g != nullptr;
   float* hr = a.h + (size_t)row * d;
@@ -144,6 +146,30 @@ __global__ void __launch_bounds__(256) k_pre_rln(PreLnArgs a) {
 // Grid y splits the k units (PRE_PART: one buffer of partial sums per split).
 // Weights: 16-column (W_F16) or 32-column (W_F32) fragment order; either is read
 // by picking each lane's 16 bytes.
+namespace {
+// Rows 8 (lane / 32) .. + 7 of half `half` (16 rows) of a 32 x 32 accumulator, this lane's
+// column, + bias, as eight bf16: the two row groups change places between half-waves.
+__device__ __forceinline__ uint4 rows8_bf16(const floatx16& c, int half, float bias) {
+  uint32_t p[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) p[e] = pack2_bf16(c[8 * half + 2 * e] + bias, c[8 * half + 2 * e + 1] + bias);
+  const auto x = __builtin_amdgcn_permlane32_swap(p[0], p[2], false, false);
+  const auto y = __builtin_amdgcn_permlane32_swap(p[1], p[3], false, false);
+  return make_uint4(x[0], y[0], x[1], y[1]);
+}
+// The same half + bias turned around in the wave's own LDS (16 x 33 floats): lane l gets
+// row l / 4, columns 8 (l % 4) .. + 7.
+__device__ __forceinline__ void turn_half(float* tr, const floatx16& c, int half, float bias, float* o) {
+  const int lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
+#pragma unroll
+  for (int v = 0; v < 8; ++v) tr[(8 * (v >> 2) + 4 * lk + (v & 3)) * 33 + lr] = c[8 * half + v] + bias;
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = tr[(lane >> 2) * 33 + 8 * (lane & 3) + e];
+  __builtin_amdgcn_wave_barrier();
+}
+}  // namespace
+
 template <int EPI, int P, int WK, int TI, int TJ, int D>
 __global__ void __launch_bounds__(256, 1) k_pre_gemm(PreGemmArgs a, int nmb, int nnb, int rs) {
   constexpr int NW = 4, TM = 32 * TI, TN = 32 * TJ, Q = TI * TJ / NW;  // Q: 32 x 32 tiles a wave finishes
@@ -265,7 +291,7 @@ __global__ void __launch_bounds__(256, 1) k_pre_gemm(PreGemmArgs a, int nmb, int
           sum[r0 + r][4 * v + 3] += o.w;
         }
   }
-  if constexpr (EPI == PRE_GELU) __syncthreads();
+  if constexpr (EPI == PRE_GELU || EPI == PRE_ENC) __syncthreads();
 
   // accumulator v of a 32 x 32 tile: row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32
 #pragma unroll
@@ -297,20 +323,36 @@ __global__ void __launch_bounds__(256, 1) k_pre_gemm(PreGemmArgs a, int nmb, int
           const PrePart p = a.parts[r0 / kPrePart];
           const size_t ph = (size_t)a.page_table[p.slot * a.pages_per_slot + p.pos0 / kPage] * a.n_head + head;
           bf16* cache = reinterpret_cast<bf16*>(a.cache) + (kind == 2 ? a.kv_stride : 0) + ph * kPage * kHeadDim;
+          if (kind == 1) {
 #pragma unroll
-          for (int g = 0; g < 2; ++g) {  // four consecutive positions per lane
-            uint32_t b[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) b[e] = bf16_bits_rne(c[8 * half + 4 * g + e] + bias);
-            const int i0 = 8 * g + 4 * lk;
-            if (kind == 1) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) cache[(i0 + e) * kHeadDim + dim].u = (uint16_t)b[e];
-            } else {
-              *reinterpret_cast<uint2*>(cache + dim * kPage + i0) = make_uint2(b[0] | b[1] << 16, b[2] | b[3] << 16);
-            }
+            for (int v = 0; v < 8; ++v)
+              cache[(8 * (v >> 2) + 4 * lk + (v & 3)) * kHeadDim + dim] = from_f<bf16>(c[8 * half + v] + bias);
+          } else {
+            *reinterpret_cast<uint4*>(cache + dim * kPage + 8 * lk) = rows8_bf16(c, half, bias);
           }
         }
+      }
+    } else if constexpr (EPI == PRE_ENC) {
+      // queries | keys as bf16 rows [row][2d], values transposed [head][dim][period] per
+      // request of `period` rows (a 32-row tile lies in one request)
+      const int kind = nt < 2 * a.d ? 0 : 1;
+      if (kind == 0) {
+        float* tr = reinterpret_cast<float*>(red) + wv * 16 * 33;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          float o[8];
+          turn_half(tr, c, half, bias, o);
+          const int row = mt0 + 16 * half + (lane >> 2);
+          if (row < a.M)
+            *reinterpret_cast<uint4*>(a.aout + (size_t)row * 2 * a.d + nt + 8 * (lane & 3)) =
+                make_uint4(pack2_bf16(o[0], o[1]), pack2_bf16(o[2], o[3]), pack2_bf16(o[4], o[5]), pack2_bf16(o[6], o[7]));
+        }
+      } else {
+        const int cc = nc - 2 * a.d, req = mt0 / a.period, f0 = mt0 - req * a.period;
+        bf16* vt = reinterpret_cast<bf16*>(a.cache) + ((size_t)req * a.d + cc) * a.period + f0;
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+          *reinterpret_cast<uint4*>(vt + 16 * half + 8 * lk) = rows8_bf16(c, half, bias);
       }
     } else {
       // GELU into the next product's planes: 16 x 32 half tiles turned around in

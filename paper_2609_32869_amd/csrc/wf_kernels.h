@@ -390,8 +390,9 @@ struct PreLnArgs {
   const bf16* b;
   bf16* out;
   int mt, d;          // 16-row tiles held by the operand buffers
+  int period, valid;  // period > 0: of every `period` rows the first `valid` are updated
 };
-enum { PRE_STORE = 0, PRE_PART = 1, PRE_GELU = 2, PRE_QKV = 3 };
+enum { PRE_STORE = 0, PRE_PART = 1, PRE_GELU = 2, PRE_QKV = 3, PRE_ENC = 4 };
 struct PreGemmArgs {
   const bf16* a;      // operand planes of K columns
   int mt;             // 16-row tiles held by operand buffers
@@ -402,7 +403,8 @@ struct PreGemmArgs {
   float* y;           // STORE rows, PART partial sums, QKV queries
   int ldy;
   size_t pstride;
-  bf16* aout;         // GELU: operand planes of N columns
+  bf16* aout;         // GELU: operand planes of N columns; ENC: queries | keys [row][2d]
+  int period;         // ENC: rows per request
   const PrePart* parts;
   const int* page_table;
   int pages_per_slot, d, n_head;

@@ -1,0 +1,57 @@
+"""The request-time matrix products on 256 x 128 tiles (bf16 storage), at sizes that end
+inside a tile, through the calls that reach them.
+
+Both sides round to bf16 at the same points and accumulate in fp32, so a difference
+is a rounding that falls the other way: the acoustic memory's bar is one bf16 ulp at
+|A| < 2 (7.8e-3), the logits' bar is the decoder's.
+"""
+import numpy as np
+import pytest
+import torch
+
+from wf_fixtures import MICRO, MICRO_ENC, make_encoder_weights, make_audio, make_weights, make_prefix
+from oracle import OracleOpts
+from oracle.encoder import Encoder
+from oracle.numerics import bf16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def encode_and_compare(ecfg, n):
+    from paper_2609_32869_amd import WhisperEncoder
+    W = make_encoder_weights(ecfg)
+    enc = WhisperEncoder.from_host(ecfg, [W.values[k] for k, _ in W.order])
+    audio = np.stack([make_audio(ecfg, s) for s in range(n)])
+    got = enc.run(torch.from_numpy(audio).cuda()).float().cpu().numpy()
+    enc.close()
+    E = Encoder(ecfg, W.values, OracleOpts(dtype=np.float32, gemm_bf16=True, exact=False))
+    for s in range(n):
+        d = np.abs(got[s] - bf16(E.encode(audio[s])))
+        print(f"{ecfg.name} request {s}: max |dA| {d.max():.2e}, mean {d.mean():.2e}", flush=True)
+        assert d.max() <= 8e-3 and d.mean() <= 5e-4
+
+
+def test_wide_mlp_product():
+    """First MLP product of 16384 columns over 300 rows (44 in the second row tile)."""
+    encode_and_compare(MICRO_ENC.with_(name="enc-wide", n_ctx=300, d_model=256, n_head=4, n_layer=1, d_ff=16384), 1)
+
+
+@pytest.mark.parametrize("n_frames", [300, 256])
+def test_acoustic_keys_and_values_of_many_blocks(n_frames):
+    """Twelve blocks' keys and transposed values in one launch: rows that end inside a
+    tile and at its edge, zero padding of the values up to 512 frames."""
+    from lockstep import Lockstep
+    cfg = MICRO.with_(name="xkv-wide", dtype="bf16", n_layer=12, d_model=512, n_head=8, d_ff=512, n_vocab=501,
+                      taps=(0, 5, 11), n_frames=n_frames)
+    W = make_weights(cfg)
+    ls = Lockstep(cfg, W, [make_prefix(cfg, 0, 7)], [20], 2e-2, opts=OracleOpts(dtype=np.float32, kv_bf16=True))
+    for _ in range(2):
+        ls.step()
+    print(f"frames {n_frames}: max |dlogit| draft {ls.max_dlogit:.2e} target {ls.max_tlogit:.2e}")
+    ls.close()
