@@ -335,7 +335,7 @@ static void enc_forward(Enc& e, const float* audio, bf16* mem, hipStream_t st) {
     }
     {  // softmax(q k^T / 8) v per head, fused (scores stay on chip)
       EncAttnArgs at{};
-      at.qk = qk; at.ldqk = 2 * d; at.vt = vt; at.Tp = L.Tp; at.o = o; at.ldo = d; at.n = n; at.d = d;
+      at.qk = qk; at.ldqk = 2 * d; at.vt = vt; at.Tp = L.Tp; at.o = o; at.ldo = d; at.n = n; at.d = d; at.nreq = 1;
       enc_attention(at, H, st);
     }
     mm(mm_args(o, d, e.W(w.wo), d, e.W(w.bo), n, d, d, x, d), MM_RESID, 1, st);

@@ -169,34 +169,29 @@ __global__ void __launch_bounds__(256) k_ln_rows(const float* __restrict__ x, co
   }
 }
 
-// Bidirectional self-attention of one head over all positions, fused: one block
-// per (128 queries, head), four waves of 32 queries.  Keys and transposed values
-// stream through four LDS stages in tiles of 64 keys, copied straight from memory
-// (global_load_lds_dwordx4) three tiles ahead of their use.  Two passes over the
-// keys: the first keeps a running maximum and rescaled sum of exp per (lane,
-// row), combined across lanes at its end into the row maximum M and sum L; the
-// second forms p = exp(s - M) / L, rounds it to bf16 (the product's input, as an
-// unfused softmax would store it) and accumulates O += p V on the matrix cores.
-// Scores s = q.k / 8 from bf16 q, k (v_mfma_f32_32x32x16_bf16, fp32
-// accumulation); the probability tile goes through per-wave LDS to become the
-// next product's A operand.
+// Bidirectional self-attention of one head over all positions, fused, one pass over
+// the keys: one block per (128 queries, head), four waves of 32 queries.  Keys and
+// transposed values stream through four LDS stages in tiles of 64 keys, copied
+// straight from memory (global_load_lds_dwordx4) three tiles ahead of their use.
+// Per 32 keys a wave forms S^T = K q^T on v_mfma_f32_32x32x16_bf16, so a lane holds 16
+// keys of one query: the running maximum and sum are per lane (one swap of
+// half-waves joins a query's two lanes), p = exp(s - m) is rounded to bf16 in place
+// and two half-wave swaps of the packed pairs make it the B operand of O^T += V^T P^T.
+// O and the sum are rescaled only where a maximum moved.  Bound by the vector units
+// (32 exponentials per lane and tile against 16 matrix instructions).  1500 positions, 20
+// heads: 31.9 us; 70 with two passes over the keys and the probabilities through LDS.
 namespace {
 typedef __attribute__((address_space(3))) void lds_void;
 constexpr int kAq = 128, kAk = 64, kAThreads = 256;
-constexpr int kPld = kAk + 8;  // row stride of a wave's probability tile (bf16)
 // stage layout (16-byte chunks): keys [key * 8 + chunk ^ (key & 7)] then
 // transposed values [512 + dim * 8 + chunk ^ (dim & 7)]
 constexpr int kStageChunks = 1024;
-constexpr int kWaitK = (4 & 15) | (7 << 4) | (0 << 8);  // vmcnt <= 4: two later tiles' key copies
 constexpr int kWaitKV = (8 & 15) | (7 << 4) | (0 << 8); // vmcnt <= 8: two later tiles' key + value copies
 constexpr int kWaitAll = (0 & 15) | (7 << 4) | (15 << 8);
 }  // namespace
-__shared__ uint4 g_att0[kStageChunks], g_att1[kStageChunks], g_att2[kStageChunks], g_att3[kStageChunks];
-__shared__ bf16 g_attp[4][32 * kPld];
 
 // copies of key tile kt (its index clamped to the last tile) into a stage: wave w
-// fills chunks (w * 2 + j) * 64 + lane of the keys (and, with values, 512 + ...)
-template <bool V>
+// fills chunks (w * 2 + j) * 64 + lane of the keys and 512 + ... of the values
 __device__ __forceinline__ void attn_copy(const EncAttnArgs& a, int head, int kt, int ntile, uint4* stage) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, k0 = min(kt, ntile - 1) * kAk;
 #pragma unroll
@@ -205,33 +200,20 @@ __device__ __forceinline__ void attn_copy(const EncAttnArgs& a, int head, int kt
     const bf16* src = a.qk + (size_t)min(k0 + r, a.n - 1) * a.ldqk + a.d + head * kHeadDim + 8 * ch;
     __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)&stage[(w * 2 + j) * 64], 16, 0, 0);
   }
-  if (V) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int slot = (w * 2 + j) * 64 + lane, r = slot >> 3, ch = (slot & 7) ^ (r & 7);
-      const bf16* src = a.vt + ((size_t)head * kHeadDim + r) * a.Tp + k0 + 8 * ch;
-      __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)&stage[512 + (w * 2 + j) * 64], 16, 0, 0);
-    }
-  }
-}
-
-// scores of this wave's 32 queries against the tile's 64 keys (two 32-key halves)
-__device__ __forceinline__ void attn_scores(const uint4* stage, const bf16x8* qf, floatx16* acc, int lr, int lk) {
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[kb][v] = 0.f;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int row = kb * 32 + lr;
-      const bf16x8 kf = __builtin_bit_cast(bf16x8, stage[row * 8 + ((2 * s + lk) ^ (row & 7))]);
-      acc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[s], kf, acc[kb], 0, 0, 0);
-    }
+  for (int j = 0; j < 2; ++j) {
+    const int slot = (w * 2 + j) * 64 + lane, r = slot >> 3, ch = (slot & 7) ^ (r & 7);
+    const bf16* src = a.vt + ((size_t)head * kHeadDim + r) * a.Tp + k0 + 8 * ch;
+    __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)&stage[512 + (w * 2 + j) * 64], 16, 0, 0);
   }
 }
 
 __global__ void __launch_bounds__(kAThreads) k_enc_attn(EncAttnArgs a) {
+  __shared__ uint4 g_att0[kStageChunks], g_att1[kStageChunks], g_att2[kStageChunks], g_att3[kStageChunks];
   const int head = blockIdx.y, q0 = blockIdx.x * kAq;
+  a.qk += (size_t)blockIdx.z * a.sqk;
+  a.vt += (size_t)blockIdx.z * a.svt;
+  a.o += (size_t)blockIdx.z * a.so;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
   const int ntile = (a.n + kAk - 1) / kAk;
   bf16x8 qf[4];
@@ -241,113 +223,111 @@ __global__ void __launch_bounds__(kAThreads) k_enc_attn(EncAttnArgs a) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
   }
-  floatx16 acc[2];
-
-  // pass 1: running maximum and sum of exp per (lane, row)
-  float m[16], l[16];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    m[v] = -FLT_MAX;
-    l[v] = 0.f;
-  }
-  auto step1 = [&](int kt, const uint4* cur, uint4* nxt) {
-    __builtin_amdgcn_s_waitcnt(kWaitK);
-    __builtin_amdgcn_s_barrier();
-    attn_copy<false>(a, head, kt + 3, ntile, nxt);  // every step issues its copies: exact wait counts
-    if (kt < ntile) {
-      attn_scores(cur, qf, acc, lr, lk);
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        const bool ok = kt * kAk + kb * 32 + lr < a.n;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float sv = acc[kb][v] * 0.125f;
-          const float mn = ok ? fmaxf(m[v], sv) : m[v];
-          l[v] = ok ? l[v] * __expf(m[v] - mn) + __expf(sv - mn) : l[v];
-          m[v] = mn;
-        }
-      }
-    }
-  };
-  attn_copy<false>(a, head, 0, ntile, g_att0);
-  attn_copy<false>(a, head, 1, ntile, g_att1);
-  attn_copy<false>(a, head, 2, ntile, g_att2);
-  for (int kt = 0; kt < ntile; kt += 4) {
-    step1(kt, g_att0, g_att3);
-    step1(kt + 1, g_att1, g_att0);
-    step1(kt + 2, g_att2, g_att1);
-    step1(kt + 3, g_att3, g_att2);
-  }
-  __builtin_amdgcn_s_waitcnt(kWaitAll);  // the surplus copies have landed before the stages are refilled
-  // combine over the 32 lanes holding a row's columns (same half of the wave)
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    float mx = m[v];
-    for (int o = 1; o < 32; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    float sm = l[v] * __expf(m[v] - mx);
-    for (int o = 1; o < 32; o <<= 1) sm += __shfl_xor(sm, o, 64);
-    m[v] = mx;
-    l[v] = 1.f / sm;
-  }
-  __syncthreads();
-
-  // pass 2: p = exp(s - M) / L in bf16, O += p V
+  // scores in units of log2(e) / 8, so the exponential is one instruction
+  constexpr float kScale = 0.125f * 1.44269504088896340736f;
+  float m = -INFINITY, l = 0.f;  // running maximum (of raw scores) and this lane's share of the sum
   floatx16 o[2];
 #pragma unroll
   for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[nt][v] = 0.f;
-  bf16* pw = g_attp[w];
-  auto step2 = [&](int kt, const uint4* cur, uint4* nxt) {
+  auto step = [&](int kt, const uint4* cur, uint4* nxt) {
     __builtin_amdgcn_s_waitcnt(kWaitKV);
     __builtin_amdgcn_s_barrier();
-    attn_copy<true>(a, head, kt + 3, ntile, nxt);
-    if (kt < ntile) {
-      attn_scores(cur, qf, acc, lr, lk);
+    attn_copy(a, head, kt + 3, ntile, nxt);  // every step issues its copies: exact wait counts
+    if (kt >= ntile) return;
+    floatx16 sc[2];
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        const bool ok = kt * kAk + kb * 32 + lr < a.n;
+    for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float pv = ok ? __expf(acc[kb][v] * 0.125f - m[v]) * l[v] : 0.f;
-          const int row = 8 * (v >> 2) + 4 * lk + (v & 3);
-          pw[row * kPld + kb * 32 + lr] = from_f<bf16>(pv);
-        }
-      }
+      for (int v = 0; v < 16; ++v) sc[kb][v] = 0.f;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const bf16x8 pf = *reinterpret_cast<const bf16x8*>(pw + lr * kPld + 16 * s + 8 * lk);
+        const int row = kb * 32 + lr;
+        const bf16x8 kf = __builtin_bit_cast(bf16x8, cur[row * 8 + ((2 * s + lk) ^ (row & 7))]);
+        sc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sc[kb], 0, 0, 0);
+      }
+    }
+    // lane: query lr, keys kt * 64 + kb * 32 + 8 (v / 4) + 4 lk + v % 4
+    if (kt * kAk + kAk > a.n) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (kt * kAk + kb * 32 + 8 * (v >> 2) + 4 * lk + (v & 3) >= a.n) sc[kb][v] = -INFINITY;
+    }
+    float mx = sc[0][0];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sc[kb][v]);
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    const float mn = fmaxf(m, fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1])));  // finite: every tile holds a key
+    if (__builtin_amdgcn_ballot_w64(mn != m)) {
+      const float f = __builtin_amdgcn_exp2f((m - mn) * kScale);  // 0 at the first tile
+      l *= f;
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[nt][v] *= f;
+      m = mn;
+    }
+    const float ms = mn * kScale;
+    float ls = 0.f;
+    uint32_t pk[2][8];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int v = 0; v < 16; v += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[kb][v], kScale, -ms)), p1 = __builtin_amdgcn_exp2f(fmaf(sc[kb][v + 1], kScale, -ms));
+        ls += p0 + p1;
+        pk[kb][v >> 1] = pack2_bf16(p0, p1);
+      }
+    l += ls;
+    // values: 16 keys (substep s of key half kb) per instruction; lanes 0..31 need the
+    // keys 16 s .. + 7 of their query, lanes 32..63 the keys 16 s + 8 .. + 15
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const auto y0 = __builtin_amdgcn_permlane32_swap(pk[kb][4 * s], pk[kb][4 * s + 2], false, false);
+        const auto y1 = __builtin_amdgcn_permlane32_swap(pk[kb][4 * s + 1], pk[kb][4 * s + 3], false, false);
+        const bf16x8 pf = __builtin_bit_cast(bf16x8, make_uint4(y0[0], y1[0], y0[1], y1[1]));
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
           const int row = nt * 32 + lr;
-          const bf16x8 vf = __builtin_bit_cast(bf16x8, cur[512 + row * 8 + ((2 * s + lk) ^ (row & 7))]);
-          o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf, vf, o[nt], 0, 0, 0);
+          const bf16x8 vf = __builtin_bit_cast(bf16x8, cur[512 + row * 8 + ((4 * kb + 2 * s + lk) ^ (row & 7))]);
+          o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf, o[nt], 0, 0, 0);
         }
       }
-    }
   };
-  attn_copy<true>(a, head, 0, ntile, g_att0);
-  attn_copy<true>(a, head, 1, ntile, g_att1);
-  attn_copy<true>(a, head, 2, ntile, g_att2);
+  attn_copy(a, head, 0, ntile, g_att0);
+  attn_copy(a, head, 1, ntile, g_att1);
+  attn_copy(a, head, 2, ntile, g_att2);
   for (int kt = 0; kt < ntile; kt += 4) {
-    step2(kt, g_att0, g_att3);
-    step2(kt + 1, g_att1, g_att0);
-    step2(kt + 2, g_att2, g_att1);
-    step2(kt + 3, g_att3, g_att2);
+    step(kt, g_att0, g_att3);
+    step(kt + 1, g_att1, g_att0);
+    step(kt + 2, g_att2, g_att1);
+    step(kt + 3, g_att3, g_att2);
   }
   __builtin_amdgcn_s_waitcnt(kWaitAll);  // no copy may land in LDS after the block has left
-  // O rows: query 8 (v / 4) + 4 lk + v % 4 of the wave, dim nt * 32 + lr
+  const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+  const float inv = 1.f / (__uint_as_float(x[0]) + __uint_as_float(x[1]));
+  // O^T: lane holds query lr, dims nt * 32 + 8 (v / 4) + 4 lk + v % 4
+  const int q = q0 + w * 32 + lr;
+  if (q < a.n) {
+    bf16* op = a.o + (size_t)q * a.ldo + head * kHeadDim;
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt)
+    for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int q = q0 + w * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
-      if (q < a.n) a.o[(size_t)q * a.ldo + head * kHeadDim + nt * 32 + lr] = from_f<bf16>(o[nt][v]);
-    }
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<uint2*>(op + nt * 32 + 8 * g + 4 * lk) =
+            make_uint2(pack2_bf16(o[nt][4 * g] * inv, o[nt][4 * g + 1] * inv), pack2_bf16(o[nt][4 * g + 2] * inv, o[nt][4 * g + 3] * inv));
+  }
 }
 
 void enc_attention(const EncAttnArgs& a, int n_head, hipStream_t st) {
-  k_enc_attn<<<dim3((a.n + kAq - 1) / kAq, n_head), kAThreads, 0, st>>>(a);
+  k_enc_attn<<<dim3((a.n + kAq - 1) / kAq, n_head, a.nreq), kAThreads, 0, st>>>(a);
 }
 
 void logmel(const LogmelArgs& a, hipStream_t st) {

@@ -355,6 +355,8 @@ struct EncAttnArgs {
   int Tp;
   bf16* o;
   int ldo, n, d;
+  int nreq;                // requests, each sqk / svt / so elements after the one before
+  long long sqk, svt, so;
 };
 void enc_attention(const EncAttnArgs& a, int n_head, hipStream_t st);
 
