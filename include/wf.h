@@ -303,7 +303,7 @@ typedef struct wf_encoder_config {
 
 typedef struct wf_encoder wf_encoder;
 
-/* Workspace bytes of an encoder handle (one request's activations). */
+/* Workspace bytes of an encoder handle (weights and four requests' activations). */
 int wf_encoder_workspace_bytes(const wf_encoder_config* cfg, size_t* bytes);
 /* Number of parameter tensors and the element count of tensor i, in manifest
  * order: conv1.w [d, n_mels, 3] conv1.b [d] conv2.w [d, d, 3] conv2.b [d]; per
@@ -320,7 +320,8 @@ int wf_encoder_init(wf_encoder** e, const wf_encoder_config* cfg, const void* co
                     void* workspace, size_t ws_bytes, void* stream);
 /* Encode n waveforms: audio device fp32 [n, 2 * n_ctx * hop]; mem device bf16
  * [n, n_ctx, d_model] (16-byte aligned), ready for wf_encode_memory_set.
- * Requests run one after another on `stream`. */
+ * Up to four requests go through the layers together, more in several passes on
+ * `stream`. */
 int wf_encoder_run(wf_encoder* e, int n, const float* audio, void* mem, void* stream);
 /* The frontend alone: scaled log-mel features of one waveform into mel, device
  * fp32 [n_mels, 2 * n_ctx]. */

@@ -34,6 +34,11 @@ struct EncLayout {
   size_t weights, pos, window, twiddle, filters, fband, gmax, logmel, rows1, z, rows2, x, a, qk, vt, o, u, total;
 };
 
+// Requests that one pass of the layers runs together (the workspace holds their
+// activations: 65 MB each at large-v3 shapes).  Their rows lie Tp apart, a multiple of
+// the products' row tiles, so one request costs the same as before.
+constexpr int kEncBatch = 4;
+
 struct Enc {
   wf_encoder_config cfg;
   EncLayout lay;
@@ -99,17 +104,19 @@ void layout(const wf_encoder_config& c, EncLayout& L) {
   L.twiddle = region((size_t)c.n_fft * 16);
   L.filters = region((size_t)c.n_mels * L.nb * 8);
   L.fband = region((size_t)c.n_mels * 8);
-  L.gmax = region(4);
-  L.logmel = region(T * c.n_mels * 4);
-  L.rows1 = region(T * L.Kp1 * 2);
-  L.z = region(T * d * 2);
-  L.rows2 = region(n * 3 * d * 2);
-  L.x = region(n * d * 4);
-  L.a = region(n * d * 2);
-  L.qk = region(n * 2 * d * 2);
-  L.vt = region(H * kHeadDim * L.Tp * 2);
-  L.o = region(n * d * 2);
-  L.u = region(n * F * 2);
+  const size_t R = kEncBatch, Tp = L.Tp;
+  L.gmax = region(R * 4);
+  L.logmel = region(R * T * c.n_mels * 4);
+  L.rows1 = region(R * T * L.Kp1 * 2);
+  L.z = region(R * T * d * 2);
+  L.rows2 = region(R * n * 3 * d * 2);
+  L.qk = region(R * Tp * 2 * d * 2);
+  L.vt = region(R * H * kHeadDim * Tp * 2);
+  L.u = region(R * Tp * F * 2);
+  // x, a and o last: the rows between requests are zero from set-up on
+  L.x = region(R * Tp * d * 4);
+  L.a = region(R * Tp * d * 2);
+  L.o = region(R * Tp * d * 2);
   L.total = o;
 }
 
@@ -248,6 +255,7 @@ int wf_encoder_init(wf_encoder** out, const wf_encoder_config* cfg, const void* 
     return efail(nullptr, WF_EHIP, std::string(what) + ": " + hipGetErrorString(err));
   };
   hipError_t err = hipMemsetAsync(workspace, 0, L.weights + L.wtotal * 2, st);  // weights incl. padding
+  if (err == hipSuccess) err = hipMemsetAsync(e.at<char>(L.x), 0, L.total - L.x, st);  // rows between requests
   if (err != hipSuccess) return bail(err, "hipMemsetAsync");
   char* wb = e.at<char>(L.weights);
   for (int i = 0; i < n_weights; ++i) {
@@ -274,9 +282,9 @@ int wf_encoder_init(wf_encoder** out, const wf_encoder_config* cfg, const void* 
   return WF_OK;
 }
 
-// The frontend of one waveform: log-mel features into the workspace (and
-// optionally the scaled features [n_mels][frames] into mel_out).
-static void enc_frontend(Enc& e, const float* audio, float* mel_out, hipStream_t st) {
+// The frontend of nreq waveforms: log-mel features into the workspace (and, of one
+// waveform, optionally the scaled features [n_mels][frames] into mel_out).
+static void enc_frontend(Enc& e, int nreq, const float* audio, float* mel_out, hipStream_t st) {
   const EncLayout& L = e.lay;
   LogmelArgs a{};
   a.audio = audio;
@@ -294,6 +302,7 @@ static void enc_frontend(Enc& e, const float* audio, float* mel_out, hipStream_t
   a.rows = e.at<bf16>(L.rows1);
   a.ld1 = L.Kp1;
   a.mel_out = mel_out;
+  a.nreq = nreq;
   logmel(a, st);
 }
 
@@ -305,45 +314,50 @@ static MmArgs mm_args(const bf16* A, long long lda, const bf16* B, long long ldb
   return a;
 }
 
-// Waveform -> acoustic memory [n_ctx][d] (bf16) for one request.
-static void enc_forward(Enc& e, const float* audio, bf16* mem, hipStream_t st) {
+// Waveforms -> acoustic memory [nreq][n_ctx][d] (bf16), nreq <= kEncBatch: the requests'
+// rows stand Tp apart and go through every product of the layers together.
+static void enc_forward(Enc& e, int nreq, const float* audio, bf16* mem, hipStream_t st) {
   const wf_encoder_config& c = e.cfg;
   const EncLayout& L = e.lay;
-  const int d = c.d_model, F = c.d_ff, H = c.n_head, n = c.n_ctx;
-  enc_frontend(e, audio, nullptr, st);
+  const int d = c.d_model, F = c.d_ff, H = c.n_head, n = c.n_ctx, Tp = L.Tp, M = nreq * Tp;
+  enc_frontend(e, nreq, audio, nullptr, st);
   bf16 *z = e.at<bf16>(L.z), *rows2 = e.at<bf16>(L.rows2), *a = e.at<bf16>(L.a), *qk = e.at<bf16>(L.qk);
   bf16 *vt = e.at<bf16>(L.vt), *o = e.at<bf16>(L.o), *u = e.at<bf16>(L.u);
   float* x = e.at<float>(L.x);
   // stem: conv1 + GELU, conv2 (stride 2) + GELU + positions
-  mm(mm_args(e.at<bf16>(L.rows1), L.Kp1, e.W(L.conv1), L.Kp1, e.W(L.conv1_b), L.T, d, L.Kp1, z, d), MM_BF16_GELU, 1, st);
-  conv_rows_s2(z, rows2, L.T, n, d, st);
+  mm(mm_args(e.at<bf16>(L.rows1), L.Kp1, e.W(L.conv1), L.Kp1, e.W(L.conv1_b), nreq * L.T, d, L.Kp1, z, d), MM_BF16_GELU, 1, st);
+  conv_rows_s2(z, rows2, L.T, n, d, nreq, st);
   {
     MmArgs m = mm_args(rows2, 3 * d, e.W(L.conv2), 3 * d, e.W(L.conv2_b), n, d, 3 * d, x, d);
+    m.sA = (long long)n * 3 * d;
+    m.sO = (long long)Tp * d;
     m.add = e.at<float>(L.pos);
     m.ldadd = d;
-    mm(m, MM_GELU_ADD_F32, 1, st);
+    mm(m, MM_GELU_ADD_F32, nreq, st);
   }
   for (const EncLayer& w : L.layers) {
-    ln_rows(x, e.W(w.ln1_g), e.W(w.ln1_b), a, n, d, d, st);
+    ln_rows(x, e.W(w.ln1_g), e.W(w.ln1_b), a, n, d, nreq, Tp, Tp, st);
     {  // q | k row-major, v transposed per head [head][dim][Tp]
-      MmArgs m = mm_args(a, d, e.W(w.wqkv), d, e.W(w.bqkv), n, 3 * d, d, qk, 2 * d);
+      MmArgs m = mm_args(a, d, e.W(w.wqkv), d, e.W(w.bqkv), M, 3 * d, d, qk, 2 * d);
       m.out2 = vt;
+      m.sO2 = (long long)d * Tp;
       m.d = d;
       m.n_head = H;
-      m.vt_frames = L.Tp;
+      m.vt_frames = m.period = Tp;
       mm(m, MM_QKV_ENC, 1, st);
     }
     {  // softmax(q k^T / 8) v per head, fused (scores stay on chip)
       EncAttnArgs at{};
-      at.qk = qk; at.ldqk = 2 * d; at.vt = vt; at.Tp = L.Tp; at.o = o; at.ldo = d; at.n = n; at.d = d; at.nreq = 1;
+      at.qk = qk; at.ldqk = 2 * d; at.vt = vt; at.Tp = Tp; at.o = o; at.ldo = d; at.n = n; at.d = d;
+      at.nreq = nreq; at.sqk = (long long)Tp * 2 * d; at.svt = (long long)d * Tp; at.so = (long long)Tp * d;
       enc_attention(at, H, st);
     }
-    mm(mm_args(o, d, e.W(w.wo), d, e.W(w.bo), n, d, d, x, d), MM_RESID, 1, st);
-    ln_rows(x, e.W(w.ln2_g), e.W(w.ln2_b), a, n, d, d, st);
-    mm(mm_args(a, d, e.W(w.w1), d, e.W(w.b1), n, F, d, u, F), MM_BF16_GELU, 1, st);
-    mm(mm_args(u, F, e.W(w.w2), F, e.W(w.b2), n, d, F, x, d), MM_RESID, 1, st);
+    mm(mm_args(o, d, e.W(w.wo), d, e.W(w.bo), M, d, d, x, d), MM_RESID, 1, st);
+    ln_rows(x, e.W(w.ln2_g), e.W(w.ln2_b), a, n, d, nreq, Tp, Tp, st);
+    mm(mm_args(a, d, e.W(w.w1), d, e.W(w.b1), M, F, d, u, F), MM_BF16_GELU, 1, st);
+    mm(mm_args(u, F, e.W(w.w2), F, e.W(w.b2), M, d, F, x, d), MM_RESID, 1, st);
   }
-  ln_rows(x, e.W(L.lnp_g), e.W(L.lnp_b), mem, n, d, d, st);
+  ln_rows(x, e.W(L.lnp_g), e.W(L.lnp_b), mem, n, d, nreq, Tp, n, st);
 }
 
 int wf_encoder_run(wf_encoder* h, int n, const float* audio, void* mem, void* stream) {
@@ -353,7 +367,10 @@ int wf_encoder_run(wf_encoder* h, int n, const float* audio, void* mem, void* st
   if (reinterpret_cast<uintptr_t>(mem) & 15) return efail(&e, WF_EINVAL, "memory output must be 16-byte aligned");
   hipStream_t st = static_cast<hipStream_t>(stream);
   const size_t ns = (size_t)e.lay.T * e.cfg.hop, per = (size_t)e.cfg.n_ctx * e.cfg.d_model;
-  for (int r = 0; r < n; ++r) enc_forward(e, audio + r * ns, static_cast<bf16*>(mem) + r * per, st);
+  // passes of at most kEncBatch requests, as even as they come
+  const int npass = (n + kEncBatch - 1) / kEncBatch, each = (n + npass - 1) / npass;
+  for (int r = 0; r < n; r += each)
+    enc_forward(e, std::min(each, n - r), audio + r * ns, static_cast<bf16*>(mem) + r * per, st);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return efail(&e, WF_EHIP, std::string("kernel launch: ") + hipGetErrorString(err));
   return WF_OK;
@@ -363,7 +380,7 @@ int wf_encoder_logmel(wf_encoder* h, const float* audio, float* mel, void* strea
   if (!h) return efail(nullptr, WF_EINVAL, "null handle");
   Enc& e = h->e;
   if (!audio || !mel) return efail(&e, WF_EINVAL, "null argument");
-  enc_frontend(e, audio, mel, static_cast<hipStream_t>(stream));
+  enc_frontend(e, 1, audio, mel, static_cast<hipStream_t>(stream));
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return efail(&e, WF_EHIP, std::string("kernel launch: ") + hipGetErrorString(err));
   return WF_OK;

@@ -43,6 +43,9 @@ __global__ void __launch_bounds__(256) k_logmel(LogmelArgs a) {
   __shared__ double pw[kMaxFft / 2 + 1];
   __shared__ float red[4];
   const int f = blockIdx.x, N = a.n_fft, nb = N / 2 + 1;
+  a.audio += (size_t)blockIdx.y * a.n_samples;
+  a.logmel += (size_t)blockIdx.y * a.n_frames * a.n_mels;
+  a.gmax += blockIdx.y;
   for (int i = threadIdx.x; i < N; i += blockDim.x) {
     int s = f * a.hop - N / 2 + i;
     s = s < 0 ? -s : s;
@@ -77,9 +80,9 @@ __global__ void __launch_bounds__(256) k_logmel(LogmelArgs a) {
   if (threadIdx.x == 0) atomicMax(a.gmax, f2key(mx));
 }
 
-// the request's maximum starts below every value
-__global__ void k_logmel_init(int* gmax) {
-  if (threadIdx.x == 0) *gmax = f2key(-FLT_MAX);
+// every request's maximum starts below every value
+__global__ void k_logmel_init(int* gmax, int nreq) {
+  if ((int)threadIdx.x < nreq) gmax[threadIdx.x] = f2key(-FLT_MAX);
 }
 
 // Clamp and scale the log-mel values ((max(x, max - 8) + 4) / 4) and gather the
@@ -87,7 +90,9 @@ __global__ void k_logmel_init(int* gmax) {
 // frames and in the padding columns up to ld), bf16.  Optionally the scaled
 // features [n_mels][frames] fp32 for inspection.
 __global__ void __launch_bounds__(256) k_logmel_rows(LogmelArgs a) {
-  const float top = key2f(*a.gmax) - 8.f;
+  a.logmel += (size_t)blockIdx.y * a.n_frames * a.n_mels;
+  a.rows += (size_t)blockIdx.y * a.n_frames * a.ld1;
+  const float top = key2f(a.gmax[blockIdx.y]) - 8.f;
   const size_t total = (size_t)a.n_frames * a.ld1;
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
     const int t = (int)(e / a.ld1), k = (int)(e % a.ld1);
@@ -107,6 +112,8 @@ __global__ void __launch_bounds__(256) k_logmel_rows(LogmelArgs a) {
 __global__ void __launch_bounds__(256) k_conv_rows_s2(const bf16* __restrict__ z, bf16* __restrict__ out, int n_in,
                                                       int n_out, int d) {
   const size_t total = (size_t)n_out * d;
+  z += (size_t)blockIdx.y * n_in * d;
+  out += (size_t)blockIdx.y * 3 * total;
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
     const int t = (int)(e / d), c = (int)(e % d);
     bf16* o = out + (size_t)t * 3 * d + 3 * c;
@@ -121,15 +128,17 @@ __global__ void __launch_bounds__(256) k_conv_rows_s2(const bf16* __restrict__ z
   }
 }
 
-// LayerNorm of fp32 rows [rows][d] into bf16 rows [rows][ldo] (one wave per row,
+// LayerNorm of fp32 rows [rows][d] of each request into bf16 rows (one wave per row,
 // biased variance, eps 1e-5, two passes over the row held in registers; d a
 // multiple of 4, each lane loading 16-byte runs of four columns).
 __global__ void __launch_bounds__(256) k_ln_rows(const float* __restrict__ x, const bf16* __restrict__ g,
                                                  const bf16* __restrict__ b, bf16* __restrict__ out, int rows, int d,
-                                                 long long ldo) {
+                                                 int in_period, int out_period) {
   constexpr int kMax = kMaxEncD / 256;  // float4 runs per lane
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= rows) return;
+  x += (size_t)blockIdx.y * in_period * d;
+  out += (size_t)blockIdx.y * out_period * d;
   const float4* xr = reinterpret_cast<const float4*>(x + (size_t)row * d);
   const int n4 = d >> 2;
   float4 v[kMax];
@@ -161,10 +170,7 @@ __global__ void __launch_bounds__(256) k_ln_rows(const float* __restrict__ x, co
       const float o1 = (v[i].y - mean) * r * to_f(g[col + 1]) + to_f(b[col + 1]);
       const float o2 = (v[i].z - mean) * r * to_f(g[col + 2]) + to_f(b[col + 2]);
       const float o3 = (v[i].w - mean) * r * to_f(g[col + 3]) + to_f(b[col + 3]);
-      uint2 pk;
-      pk.x = bf16_bits_rne(o0) | (bf16_bits_rne(o1) << 16);
-      pk.y = bf16_bits_rne(o2) | (bf16_bits_rne(o3) << 16);
-      *reinterpret_cast<uint2*>(out + (size_t)row * ldo + col) = pk;
+      *reinterpret_cast<uint2*>(out + (size_t)row * d + col) = make_uint2(pack2_bf16(o0, o1), pack2_bf16(o2, o3));
     }
   }
 }
@@ -331,17 +337,18 @@ void enc_attention(const EncAttnArgs& a, int n_head, hipStream_t st) {
 }
 
 void logmel(const LogmelArgs& a, hipStream_t st) {
-  k_logmel_init<<<1, 64, 0, st>>>(a.gmax);
-  k_logmel<<<a.n_frames, 256, 0, st>>>(a);
+  k_logmel_init<<<1, 64, 0, st>>>(a.gmax, a.nreq);
+  k_logmel<<<dim3(a.n_frames, a.nreq), 256, 0, st>>>(a);
   const size_t total = (size_t)a.n_frames * a.ld1;
-  k_logmel_rows<<<(unsigned)std::min<size_t>((total + 255) / 256, 4096), 256, 0, st>>>(a);
+  k_logmel_rows<<<dim3((unsigned)std::min<size_t>((total + 255) / 256, 4096), a.nreq), 256, 0, st>>>(a);
 }
-void conv_rows_s2(const bf16* z, bf16* out, int n_in, int n_out, int d, hipStream_t st) {
+void conv_rows_s2(const bf16* z, bf16* out, int n_in, int n_out, int d, int nreq, hipStream_t st) {
   const size_t total = (size_t)n_out * d;
-  k_conv_rows_s2<<<(unsigned)std::min<size_t>((total + 255) / 256, 4096), 256, 0, st>>>(z, out, n_in, n_out, d);
+  k_conv_rows_s2<<<dim3((unsigned)std::min<size_t>((total + 255) / 256, 4096), nreq), 256, 0, st>>>(z, out, n_in, n_out, d);
 }
-void ln_rows(const float* x, const bf16* g, const bf16* b, bf16* out, int rows, int d, long long ldo, hipStream_t st) {
-  k_ln_rows<<<(rows + 3) / 4, 256, 0, st>>>(x, g, b, out, rows, d, ldo);
+void ln_rows(const float* x, const bf16* g, const bf16* b, bf16* out, int rows, int d, int nreq, int in_period,
+             int out_period, hipStream_t st) {
+  k_ln_rows<<<dim3((rows + 3) / 4, nreq), 256, 0, st>>>(x, g, b, out, rows, d, in_period, out_period);
 }
 
 }  // namespace wf

@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(NT) k_mm(MmArgs a, int nmb, int nnb, int rs) {
     // transposed part: items (column, 8 frames)
     for (int it = t; it < BN * (BM / 8); it += NT) {
       const int cl = it / (BM / 8), r8 = (it % (BM / 8)) * 8, n = n0 + cl, f = m0 + r8;
-      if (n < nrow || n >= a.N || f >= a.vt_frames) continue;
+      if (n < nrow || n >= a.N || f >= (a.period > 0 ? a.M : a.vt_frames)) continue;
       const int col = n - nrow, head = col >> 6, dim = col & 63;
       float v[8];
 #pragma unroll
@@ -211,9 +211,10 @@ __global__ void __launch_bounds__(NT) k_mm(MmArgs a, int nmb, int nnb, int rs) {
       if (EP == MM_XKV) {
         bf16* vt = out + (size_t)a.n_head * a.M * kHeadDim + (size_t)head * kHeadDim * a.vt_frames;
         *reinterpret_cast<uint4*>(vt + vt_index(dim, f)) = pk;
-      } else {
-        bf16* vt = reinterpret_cast<bf16*>(a.out2) + (size_t)z * a.sO2;
-        *reinterpret_cast<uint4*>(vt + ((size_t)head * kHeadDim + dim) * a.vt_frames + f) = pk;
+      } else {  // the tile's rows belong to one request
+        const int req = a.period > 0 ? f / a.period : 0;
+        bf16* vt = reinterpret_cast<bf16*>(a.out2) + (size_t)(z + req) * a.sO2;
+        *reinterpret_cast<uint4*>(vt + ((size_t)head * kHeadDim + dim) * a.vt_frames + f - req * a.period) = pk;
       }
     }
     return;
@@ -411,15 +412,16 @@ __global__ void __launch_bounds__(512, 2) k_mmw(MmArgs a, int nmb, int nnb, int 
           }
           const auto x = __builtin_amdgcn_permlane32_swap(p[0], p[2], false, false);
           const auto y = __builtin_amdgcn_permlane32_swap(p[1], p[3], false, false);
-          if (f >= a.vt_frames) continue;
+          if (f >= (a.period > 0 ? a.M : a.vt_frames)) continue;
           const uint4 pk = make_uint4(x[0], y[0], x[1], y[1]);
           if (EP == MM_XKV) {
             bf16* vt = reinterpret_cast<bf16*>(a.out) + (size_t)z * a.sO + (size_t)a.n_head * a.M * kHeadDim +
                        (size_t)head * kHeadDim * a.vt_frames;
             *reinterpret_cast<uint4*>(vt + vt_index(dim, f)) = pk;
           } else {
-            bf16* vt = reinterpret_cast<bf16*>(a.out2) + (size_t)z * a.sO2;
-            *reinterpret_cast<uint4*>(vt + ((size_t)head * kHeadDim + dim) * a.vt_frames + f) = pk;
+            const int req = a.period > 0 ? f / a.period : 0;
+            bf16* vt = reinterpret_cast<bf16*>(a.out2) + (size_t)(z + req) * a.sO2;
+            *reinterpret_cast<uint4*>(vt + ((size_t)head * kHeadDim + dim) * a.vt_frames + f - req * a.period) = pk;
           }
         }
       }
@@ -438,7 +440,7 @@ int mm_check(const MmArgs& a, int ep) {
     return -1;
   if (ep == MM_GELU_ADD_F32 && (!a.add || a.ldadd < a.N)) return -1;
   if (ep == MM_XKV && (a.N != 2 * a.d || a.d % kHeadDim || a.vt_frames < a.M || a.vt_frames % kVtPiece)) return -1;
-  if (ep == MM_QKV_ENC && (a.N != 3 * a.d || a.d % kHeadDim || a.vt_frames < a.M || a.vt_frames % 8 || a.ldo % 8 ||
+  if (ep == MM_QKV_ENC && (a.N != 3 * a.d || a.d % kHeadDim || (a.period > 0 ? a.period != a.vt_frames || a.M % a.period : a.vt_frames < a.M) || a.vt_frames % 8 || a.ldo % 8 ||
                            a.ldo < 2 * a.d))
     return -1;
   return 0;

@@ -322,6 +322,9 @@ struct MmArgs {
   const float* add;  // MM_GELU_ADD_F32: fp32 rows added after the activation
   long long ldadd;
   int nb;            // rows of B present (0: N); columns past them re-read its last row
+  // MM_QKV_ENC over several requests: rows of one request (a multiple of 64, vt_frames);
+  // the values of request r lie r sO2 elements on.  0: one request
+  int period;
 };
 int mm_check(const MmArgs& a, int ep);
 void mm(const MmArgs& a, int ep, int batch, hipStream_t st);
@@ -341,10 +344,13 @@ struct LogmelArgs {
   bf16* rows;             // [n_frames][ld1] first-convolution rows
   int ld1;
   float* mel_out;         // [n_mels][n_frames] scaled features, or null
+  int nreq;               // requests, one after the other in audio, logmel, gmax and rows
 };
 void logmel(const LogmelArgs& a, hipStream_t st);
-void conv_rows_s2(const bf16* z, bf16* out, int n_in, int n_out, int d, hipStream_t st);
-void ln_rows(const float* x, const bf16* g, const bf16* b, bf16* out, int rows, int d, long long ldo, hipStream_t st);
+void conv_rows_s2(const bf16* z, bf16* out, int n_in, int n_out, int d, int nreq, hipStream_t st);
+// LayerNorm of `rows` rows of each request: rows r * in_period + i -> r * out_period + i
+void ln_rows(const float* x, const bf16* g, const bf16* b, bf16* out, int rows, int d, int nreq, int in_period,
+             int out_period, hipStream_t st);
 // fused bidirectional attention of the encoder: q | k rows [n][ldqk] (q at column
 // head * 64, k at d + head * 64), values transposed per head [head][64][Tp] (zero
 // past n), output rows [n][ldo] at column head * 64; Tp a multiple of 64

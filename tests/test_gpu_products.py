@@ -42,6 +42,13 @@ def test_wide_mlp_product():
     encode_and_compare(MICRO_ENC.with_(name="enc-wide", n_ctx=300, d_model=256, n_head=4, n_layer=1, d_ff=16384), 1)
 
 
+@pytest.mark.parametrize("n", [4, 5])
+def test_requests_share_a_pass(n):
+    """Requests that go through the layers together (four at most: five in 3 + 2), 50
+    positions each with 14 rows between them."""
+    encode_and_compare(MICRO_ENC.with_(name="enc-batch", n_ctx=50), n)
+
+
 @pytest.mark.parametrize("n_frames", [300, 256])
 def test_acoustic_keys_and_values_of_many_blocks(n_frames):
     """Twelve blocks' keys and transposed values in one launch: rows that end inside a
