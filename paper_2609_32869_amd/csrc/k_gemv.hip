@@ -16,6 +16,7 @@
 // operand, v_mfma_f32_16x16x4f32.
 #include "../../include/wf.h"
 #include "wf_operand.h"
+#include "wf_tile.h"
 
 namespace wf {
 
@@ -107,35 +108,6 @@ __device__ __forceinline__ void qkv_append(const GemvArgs& a, int n, float v, in
   cache[i] = from_f<S>(v);
 }
 
-// Bias and residual values of a multi-slot tile (TM rows x TC columns), loaded at
-// kernel start like EpiPre so the epilogue starts without a global read.
-template <int TM, int TC, int NT>
-struct RowsPre {
-  static constexpr int P = (TM * TC + NT - 1) / NT;
-  uint32_t bb[P];  // bf16 bias bits
-  float r[P];
-
-  template <typename S, int EPI>
-  __device__ __forceinline__ void load(const GemvArgs& a, int m0, int nb) {
-    const bool has_bias = a.bias != nullptr;  // without one, read the weights and discard
-    const uint16_t* bias = reinterpret_cast<const uint16_t*>(has_bias ? a.bias : a.w);
-#pragma unroll
-    for (int it = 0; it < P; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      const int row = min(m0 + idx / TC, a.R9 - 1), n = min(nb + idx % TC, a.N - 1);
-      bb[it] = bias[n];
-      r[it] = EPI == EPI_RESID ? a.y[(size_t)row * a.ldy + n] : 0.f;
-    }
-  }
-  __device__ __forceinline__ void arrive() {
-#pragma unroll
-    for (int it = 0; it < P; ++it) {
-      __asm__ volatile("" : "+v"(bb[it]));
-      __asm__ volatile("" : "+v"(r[it]));
-    }
-  }
-};
-
 // Output value v of (row, column n) for the store, GELU, residual and partial-sum
 // epilogues; res = current residual value (EPI_RESID).  The k/v append and the
 // head scores are written by the epilogue loops from prefetched values.
@@ -184,13 +156,11 @@ __device__ __forceinline__ void head_score(const GemvArgs& a, int row, int n, bo
 
 // sv holds the wave-summed tile: TM operand rows (split terms) x TC columns; ov and
 // oz are the head's score and z buffers (EPI_ARGMAX).
-// RP: rp holds the bias / residual of a multi-slot tile prefetched at kernel start
-// (bf16); otherwise the epilogue loads them.
 // LN: batch 1 with the LayerNorm folded in; sv holds (x*g) W^T and lnst the rows'
 // means (lnst[r]) and 1/sqrt(var + eps) (lnst[9 + r]).
-template <typename S, int EPI, int TM, int TC, int NT, bool RP = false, bool LN = false>
+template <typename S, int EPI, int TM, int TC, int NT, bool LN = false>
 __device__ __forceinline__ void finish_tile(const GemvArgs& a, float (*sv)[TC + 1], float (*ov)[TC], float (*oz)[TC], int m0, int nb,
-                            const EpiPre<TC, NT, LN>& pre, RowsPre<TM, TC, NT>& rp, const float* lnst = nullptr) {
+                            const EpiPre<TC, NT, LN>& pre, const float* lnst = nullptr) {
   const bool split3 = a.nsplit == 3;
   const int R = a.slot0 * kRows, Rend = (a.slot0 + a.nslots) * kRows;
   const int nrows = split3 ? kRows : TM;
@@ -247,7 +217,6 @@ __device__ __forceinline__ void finish_tile(const GemvArgs& a, float (*sv)[TC + 
     // unconditionally (indexes clamped into the buffers, unused values discarded),
     // so their latencies overlap instead of adding up element by element.
     constexpr int P = (TM * TC + NT - 1) / NT;
-    if constexpr (RP) rp.arrive();
     // without one, read the weights and discard; split-K partial sums added to y
     // (EPI_ACC) take the bias from the first k-split only
     const bool has_bias = a.bias != nullptr && !(EPI == EPI_ACC && blockIdx.y != 0);
@@ -259,14 +228,9 @@ __device__ __forceinline__ void finish_tile(const GemvArgs& a, float (*sv)[TC + 
     for (int it = 0; it < P; ++it) {
       const int idx = threadIdx.x + it * NT;
       const int ml = idx / TC, c = idx % TC, row = min(m0 + ml, rmax), n = min(nb + c, nmax);
-      if constexpr (RP) {
-        bv[it] = has_bias ? __uint_as_float(rp.bb[it] << 16) : 0.f;
-        rv[it] = rp.r[it];
-      } else {
-        const float bb = to_f(bias[n]);
-        bv[it] = has_bias ? bb : 0.f;
-        rv[it] = EPI == EPI_RESID ? a.y[(size_t)row * a.ldy + n] : 0.f;
-      }
+      const float bb = to_f(bias[n]);
+      bv[it] = has_bias ? bb : 0.f;
+      rv[it] = EPI == EPI_RESID ? a.y[(size_t)row * a.ldy + n] : 0.f;
       iv[it] = -1;
       pv[it] = 0;
       if constexpr (EPI == EPI_QKV) {
@@ -403,8 +367,7 @@ __global__ void __launch_bounds__(NW * 64) k_gemv16(GemvArgs a) {
     }
     __syncthreads();
     {
-      RowsPre<32, 16, NW * 64> none;
-      finish_tile<bf16, EPI, 32, 16, NW * 64>(a, sv, ov, oz, tile0 * 16, blockIdx.x * 16, pre, none);
+      finish_tile<bf16, EPI, 32, 16, NW * 64>(a, sv, ov, oz, tile0 * 16, blockIdx.x * 16, pre);
     }
     if (a.nsplit == 3) break;
   }
@@ -484,8 +447,7 @@ __global__ void __launch_bounds__(NW * 64) k_gemv16w(GemvArgs a) {
     }
     __syncthreads();
     {
-      RowsPre<32, TC, NW * 64> none;
-      finish_tile<bf16, EPI, 32, TC, NW * 64>(a, sv, ov, oz, tile0 * 16, blockIdx.x * TC, pre, none);
+      finish_tile<bf16, EPI, 32, TC, NW * 64>(a, sv, ov, oz, tile0 * 16, blockIdx.x * TC, pre);
     }
     if (a.nsplit == 3) break;
   }
@@ -556,366 +518,77 @@ __global__ void __launch_bounds__(NW * 64) k_gemv16k(GemvArgs a) {
   }
   __syncthreads();
   {
-    RowsPre<32, TC, NW * 64> none;
-    finish_tile<bf16, EPI, 32, TC, NW * 64>(a, sv, nullptr, nullptr, a.mt0 * 16, blockIdx.x * TC, pre, none);
+    finish_tile<bf16, EPI, 32, TC, NW * 64>(a, sv, nullptr, nullptr, a.mt0 * 16, blockIdx.x * TC, pre);
   }
 }
 
 // ---------------------------------------------------------------- bf16 GEMM (batch >= 2)
-// The rows of several slots (nine each) times W^T over 64 x 64 block tiles: each of
-// the four waves computes a 32 x 32 sub-tile (2 x 2 fragments of
-// v_mfma_f32_16x16x32_bf16), loading operand and weight fragments straight from
-// their fragment orders (1 KB per wave load).  The operand holds each value as
-// two bf16 planes (hi + lo, 2^-17 relative), both multiplied into one
-// accumulator, so the product is accurate to fp32 rounding.  Loads are double-buffered: the
-// fragments of the next kGemmU k-steps are in flight while the current ones
-// multiply.  Grid y splits the k-steps (EPI_PART stores each split's partial
-// sums).  Block b runs on XCD b % 8; the row blocks of one column block are
-// numbered so they share an XCD and its L2 serves them the weight tile.
-typedef __attribute__((address_space(3))) void lds_void;
-constexpr int kGemmU = 2;
-// From this many 64-row blocks (two-plane operand over ~2 MB) the XCDs split the
-// rows in two halves and the columns in four quarters, so each XCD's L2 keeps its
-// half of the operand while the weight tiles stream (weights are then read by two
-// XCDs, the operand no longer cycles through all eight L2s).
-constexpr int kGemmSplitRows = 6;
-__host__ __device__ __forceinline__ unsigned gemm_grid(int nmb, int nnb) {
-  return nmb >= kGemmSplitRows ? 8u * ((nmb + 1) / 2) * ((nnb + 3) / 4) : 8u * ((nnb + 7) / 8) * nmb;
-}
-template <int EPI>
-__global__ void __launch_bounds__(256) k_gemm16(GemvArgs a, int mb0, int nmb, int nnb) {
-  StampScope stamp_scope(a.stamp, 256);
-  __shared__ float sv[64][65];
-  __shared__ float ov[EPI == EPI_ARGMAX ? 64 : 1][64];
-  __shared__ float oz[EPI == EPI_ARGMAX ? 64 : 1][64];
-  const int x = blockIdx.x & 7, i = blockIdx.x >> 3;
-  int nbk, mbk;
-  if (nmb >= kGemmSplitRows) {  // XCD x: row half x & 1, column quarter x >> 1 (row blocks fastest)
-    const int nrh = (nmb + 1) / 2, ncq = (nnb + 3) / 4, rb0 = (x & 1) * nrh;
-    mbk = rb0 + i % nrh;
-    nbk = (x >> 1) * ncq + i / nrh;
-    if (mbk >= nmb || i / nrh >= ncq || nbk >= nnb) return;
-  } else {  // XCD x: column blocks x, x + 8, ..., each with every row block
-    nbk = x + 8 * (i / nmb);
-    mbk = i % nmb;
-    if (nbk >= nnb) return;
-  }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int wm = wv >> 1, wn = wv & 1;
-  const int KS = a.K / 32, MT = a.a.mt, ntile = (a.N + 15) / 16;
-  const int kper = KS / gridDim.y, ks0 = blockIdx.y * kper, ks1 = ks0 + kper;
-  const int mt0 = (mb0 + mbk) * 4 + wm * 2, nt0 = nbk * 4 + wn * 2;  // 16-row / 16-column tiles
-  RowsPre<64, 64, 256> rp;
-  rp.template load<bf16, EPI>(a, (mb0 + mbk) * 64, nbk * 64);
-  const bf16x8* Ab = reinterpret_cast<const bf16x8*>(a.a.p) + lane;
-  const bf16x8* Wb = reinterpret_cast<const bf16x8*>(a.w) + lane;
-  // Tiles past the operand's rows or the matrix's columns re-read the last one:
-  // their products only reach output rows / columns the epilogue skips, and the
-  // loads stay unconditional, so the compiler can wait for one buffer at a time.
-  const int ma0 = min(mt0, MT - 1), ma1 = min(mt0 + 1, MT - 1);
-  const int na0 = min(nt0, ntile - 1), na1 = min(nt0 + 1, ntile - 1);
-  floatx4 acc[2][2];
+// The rows of several slots (nine each) times W^T in tiles of 64 rows x 64 columns whose
+// four waves split k (split_tile, wf_tile.h).  The operand holds each value as two bf16
+// planes (hi + lo, 2^-17 relative), both multiplied into one accumulator, so the product
+// is accurate to fp32 rounding.  Grid y splits the k-steps (EPI_PART stores each split's
+// partial sums, EPI_ACC adds them to y).
+// Bound by the first, cold reads of the weights with few rows (a step reads 1.4 GB of
+// them, the caches hold none of it) and by L2 -> CU traffic with many.  Two blocks per CU:
+// one block's epilogue runs beside the other's loop.  64 x 128 tiles, one block per CU,
+// take 56 us where these take 37 (864 rows, 5120 columns in a step), although both take
+// 33 on weights that are in the memory-side cache.
+// Against waves that split the tile (fragments read twice per block, two k-steps ahead),
+// us per launch in a step, 144 rows: q|k|v 18.3 -> 12.1, W_1 17.2 -> 12.7, W_2 17.4 ->
+// 16.6; and against 64 x 320 tiles of waves 32 x 160, 864 rows: W_1 40.6 -> 37.3, W_2
+// 38.8 -> 38.5, q|k|v 31.5 -> 33.1.  A step of 8, 16 and 96 slots 4.20 -> 3.39, 5.09 ->
+// 4.49 and 13.68 -> 12.84 ms (large-v3), the head's new epilogue among it.
+
+// Bias (8 bf16) and, for EPI_RESID, the residual values of a thread's two items of a 64 x 64
+// tile (item: 8 consecutive columns of one row), loaded before the product so that the
+// epilogue starts without a global read.
+struct Rows8 {
+  uint4 bias[2];
+  float4 r[2][2];
+
+  template <int EPI>
+  __device__ __forceinline__ void load(const GemvArgs& a, int m0, int n0) {
 #pragma unroll
-  for (int p = 0; p < 2; ++p)
-#pragma unroll
-    for (int q = 0; q < 2; ++q) acc[p][q] = floatx4{0.f, 0.f, 0.f, 0.f};
-  // the operand's two bf16 planes (hi, lo): both multiply the same weight fragment
-  const size_t plane = (size_t)MT * KS * 64;
-  bf16x8 af[2][kGemmU][2][2], wf[2][kGemmU][2];
-  auto load = [&](int b, int st) {  // k-steps st.. (past the range: re-read the last one)
-#pragma unroll
-    for (int u = 0; u < kGemmU; ++u) {
-      const int ss = min(st + u, ks1 - 1);
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        af[b][u][0][h] = Ab[h * plane + ((size_t)ss * MT + ma0) * 64];
-        af[b][u][1][h] = Ab[h * plane + ((size_t)ss * MT + ma1) * 64];
+    for (int it = 0; it < 2; ++it) {
+      const int item = threadIdx.x + 256 * it, row = min(m0 + (item >> 3), a.R9 - 1), n = min(n0 + 8 * (item & 7), a.N - 8);
+      bias[it] = a.bias != nullptr ? reinterpret_cast<const uint4*>(a.bias)[n / 8] : make_uint4(0, 0, 0, 0);
+      if constexpr (EPI == EPI_RESID) {
+        const float4* y = reinterpret_cast<const float4*>(a.y + (size_t)row * a.ldy + n);
+        r[it][0] = y[0];
+        r[it][1] = y[1];
       }
-      wf[b][u][0] = Wb[((size_t)na0 * KS + ss) * 64];
-      wf[b][u][1] = Wb[((size_t)na1 * KS + ss) * 64];
     }
-  };
-  auto mul = [&](int b, int st) {
-#pragma unroll
-    for (int u = 0; u < kGemmU; ++u)
-      if (st + u < ks1) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-              acc[p][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[b][u][p][h], wf[b][u][q], acc[p][q], 0, 0, 0);
-      }
-  };
-  load(0, ks0);
-  for (int st = ks0; st < ks1; st += 2 * kGemmU) {
-    load(1, st + kGemmU);
-    mul(0, st);
-    load(0, st + 2 * kGemmU);
-    mul(1, st + kGemmU);
   }
-  // result fragment: lane l holds column l % 16, rows 4 (l / 16) + v
-#pragma unroll
-  for (int p = 0; p < 2; ++p)
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        sv[wm * 32 + p * 16 + 4 * (lane >> 4) + v][wn * 32 + q * 16 + (lane & 15)] = acc[p][q][v];
-  __syncthreads();
-  EpiPre<64, 256> pre;  // batch-1 prefetch, unused here
-  finish_tile<bf16, EPI, 64, 64, 256, true>(a, sv, ov, oz, (mb0 + mbk) * 64, nbk * 64, pre, rp);
-}
+};
 
-// The same GEMM with the fragments staged through LDS: each k-step's twelve
-// distinct 1 KB fragments (four 16-row operand tiles x two planes, four 16-column
-// weight tiles) are copied once per block straight from memory into one of four
-// 12 KB LDS stages (global_load_lds_dwordx4, three per wave), three k-steps ahead,
-// and every wave reads its six fragments from LDS.  The loads through each CU's
-// address units halve (24 KB per k-step became 12 KB), the kernel's limit.  The
-// stages are separate LDS objects and the loop is unrolled over them, so the
-// compiler sees that a copy into one stage cannot alias reads of another and keeps
-// the copies in flight; each step waits for its own stage's copies (vmcnt) and its
-// earlier LDS reads (lgkmcnt) before a plain barrier.
-__shared__ uint4 g_stage0[12][64], g_stage1[12][64], g_stage2[12][64], g_stage3[12][64];
-constexpr unsigned kGemmStagedBlocks = 256;
-constexpr int kStageWait = (6 & 15) | (7 << 4) | (0 << 8);  // vmcnt <= 6 (two later k-steps' copies), lgkmcnt 0
-
+// Epilogue of a 64 x 64 tile, 8 consecutive columns of one row at a time: every store is
+// a 16-byte run.
 template <int EPI>
-__global__ void __launch_bounds__(256) k_gemm16s(GemvArgs a, int mb0, int nmb, int nnb) {
-  StampScope stamp_scope(a.stamp, 256);
-  __shared__ float sv[64][65];
-  if (a.pf.blocks > 0 && blockIdx.x >= gridDim.x - a.pf.blocks) {  // appended blocks: a later product's weights
-    if (blockIdx.y == 0) touch_range(a.pf, blockIdx.x - (gridDim.x - a.pf.blocks));
-    return;
-  }
-  const int x = blockIdx.x & 7, i = blockIdx.x >> 3;
-  int nbk, mbk;
-  if (nmb >= kGemmSplitRows) {
-    const int nrh = (nmb + 1) / 2, ncq = (nnb + 3) / 4, rb0 = (x & 1) * nrh;
-    mbk = rb0 + i % nrh;
-    nbk = (x >> 1) * ncq + i / nrh;
-    if (mbk >= nmb || i / nrh >= ncq || nbk >= nnb) return;
-  } else {
-    nbk = x + 8 * (i / nmb);
-    mbk = i % nmb;
-    if (nbk >= nnb) return;
-  }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int wm = wv >> 1, wn = wv & 1;
-  const int KS = a.K / 32, MT = a.a.mt, ntile = (a.N + 15) / 16;
-  const int kper = KS / gridDim.y, ks0 = blockIdx.y * kper, ks1 = ks0 + kper;
-  RowsPre<64, 64, 256> rp;
-  rp.template load<bf16, EPI>(a, (mb0 + mbk) * 64, nbk * 64);
-  // this wave's three fragments of every k-step: f < 8 operand tile f >> 1, plane
-  // f & 1; f >= 8 weight tile f - 8 (tiles past the data re-read the last one)
-  const bf16x8* src[3];
-  size_t sstride[3];
-  const size_t plane = (size_t)MT * KS * 64;
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const int f = 3 * wv + j;
-    if (f < 8) {
-      const int mt = min((mb0 + mbk) * 4 + (f >> 1), MT - 1);
-      src[j] = reinterpret_cast<const bf16x8*>(a.a.p) + (f & 1) * plane + (size_t)mt * 64 + lane;
-      sstride[j] = (size_t)MT * 64;
-    } else {
-      const int nt = min(nbk * 4 + f - 8, ntile - 1);
-      src[j] = reinterpret_cast<const bf16x8*>(a.w) + (size_t)nt * KS * 64 + lane;
-      sstride[j] = 64;
-    }
-  }
-  auto copy = [&](int st, uint4 (*stg)[64]) {  // k-step st (past the range: the last one)
-    const size_t ss = (size_t)min(st, ks1 - 1);
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      __builtin_amdgcn_global_load_lds((const void*)(src[j] + ss * sstride[j]), (lds_void*)&stg[3 * wv + j][0], 16, 0, 0);
-  };
-  floatx4 acc[2][2];
-#pragma unroll
-  for (int p = 0; p < 2; ++p)
-#pragma unroll
-    for (int q = 0; q < 2; ++q) acc[p][q] = floatx4{0.f, 0.f, 0.f, 0.f};
-  auto step = [&](int st, uint4 (*cur)[64], uint4 (*nxt)[64]) {
-    __builtin_amdgcn_s_waitcnt(kStageWait);
-    __builtin_amdgcn_s_barrier();
-    copy(st + 3, nxt);  // every step issues three copies, so the wait count stays exact
-    if (st < ks1) {
-      bf16x8 af[2][2], wf[2];
-#pragma unroll
-      for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) af[p][h] = __builtin_bit_cast(bf16x8, cur[2 * (2 * wm + p) + h][lane]);
-#pragma unroll
-      for (int q = 0; q < 2; ++q) wf[q] = __builtin_bit_cast(bf16x8, cur[8 + 2 * wn + q][lane]);
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-          for (int q = 0; q < 2; ++q)
-            acc[p][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[p][h], wf[q], acc[p][q], 0, 0, 0);
-    }
-  };
-  copy(ks0, g_stage0);
-  copy(ks0 + 1, g_stage1);
-  copy(ks0 + 2, g_stage2);
-  for (int st = ks0; st < ks1; st += 4) {
-    step(st, g_stage0, g_stage3);
-    step(st + 1, g_stage1, g_stage0);
-    step(st + 2, g_stage2, g_stage1);
-    step(st + 3, g_stage3, g_stage2);
-  }
-  // no copy may land in LDS after the block has left
-  __builtin_amdgcn_s_waitcnt((0 & 15) | (7 << 4) | (15 << 8));
-#pragma unroll
-  for (int p = 0; p < 2; ++p)
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        sv[wm * 32 + p * 16 + 4 * (lane >> 4) + v][wn * 32 + q * 16 + (lane & 15)] = acc[p][q][v];
-  __syncthreads();
-  EpiPre<64, 256> pre;  // batch-1 prefetch, unused here
-  float ov[1][64], oz[1][64];  // (no argmax here)
-  finish_tile<bf16, EPI, 64, 64, 256, true>(a, sv, ov, oz, (mb0 + mbk) * 64, nbk * 64, pre, rp);
-}
-
-// ---------------------------------------------------------------- several slots, wide tiles
-// Products of many slots' rows (hundreds of rows) on v_mfma_f32_32x32x16_bf16,
-// which issues twice the work per cycle of the 16x16x32 form here.  The data keep
-// their 16x32 fragment order: the 32x32x16 operand of lane l is row l % 32 of a
-// 32-row tile and k chunk 2 s + l / 32 of k-substep s, i.e. lane (l % 16) + 16 (2 s +
-// l / 32) of 16-row fragment 2 j + (l % 32) / 16, so every load is 16 bytes from a
-// 256-byte run.  Block tile 64 rows x 32 CN columns, four independent waves of 32 x
-// 16 CN (no LDS in the main loop, no barrier): each wave loads its own operand and
-// weight fragments straight into registers kWideD k-steps ahead (about 160 KB in
-// flight per CU; LDS-staged copies behind a barrier per k-step stayed latency-bound
-// at a third of that).  XCD x takes row half x & 1 and column quarter x >> 1, so the
-// blocks sharing an L2 share their operand rows and weight columns.  The finished
-// tile is staged in LDS and written 8 consecutive columns per item (16-byte stores).
-constexpr int kWideD = 4;             // k-steps in flight per wave (the k-step count must be a multiple)
-constexpr int kWideMinRowBlocks = 8;  // 64-row blocks from which the wide kernel is used (about 57 slots)
-constexpr int kWideMaxCN = 10;        // widest tile: 32 kWideMaxCN columns
-
-__host__ __device__ __forceinline__ unsigned wide_grid(int nmb, int nnb) {
-  return 8u * ((nmb + 1) / 2) * ((nnb + 3) / 4);
-}
-
-template <int EPI, int CN>
-__global__ void __launch_bounds__(256) k_gemm32r(GemvArgs a, int mb0, int nmb, int nnb) {
-  static_assert(CN <= kWideMaxCN && CN % 2 == 0, "tile width");
-  StampScope stamp_scope(a.stamp, 256);
-  constexpr int WCT = CN / 2, TC = 32 * CN;
-  __shared__ float sv[64][TC + 1];  // the finished tile
-  if (a.pf.blocks > 0 && blockIdx.x >= gridDim.x - a.pf.blocks) {  // appended blocks: a later product's weights
-    if (blockIdx.y == 0) touch_range(a.pf, blockIdx.x - (gridDim.x - a.pf.blocks));
-    return;
-  }
-  int mbk, nbk;
-  {
-    const int x = blockIdx.x & 7, i = blockIdx.x >> 3;
-    const int nrh = (nmb + 1) / 2, ncq = (nnb + 3) / 4;
-    mbk = (x & 1) * nrh + i % nrh;
-    nbk = (x >> 1) * ncq + i / nrh;
-    if (i >= nrh * ncq || mbk >= nmb || nbk >= nnb) return;
-  }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wm = wv >> 1, wn = wv & 1;
-  const int KS = a.K / 32, MT = a.a.mt, ntile = (a.N + 15) / 16;
-  const size_t plane = (size_t)MT * KS * 64;
-  const int r32 = lane & 31, kh = lane >> 5, fsub = r32 >> 4, fl = (r32 & 15) + 16 * kh;
-  // rows and columns past the data re-read the last tile; their results are not written
-  const int mt = min((mb0 + mbk) * 4 + 2 * wm + fsub, MT - 1);
-  const bf16x8* pa = reinterpret_cast<const bf16x8*>(a.a.p) + (size_t)mt * 64 + fl;
-  const bf16x8* pb[WCT];
-#pragma unroll
-  for (int q = 0; q < WCT; ++q)
-    pb[q] = reinterpret_cast<const bf16x8*>(a.w) + (size_t)min(2 * (nbk * CN + wn * WCT + q) + fsub, ntile - 1) * KS * 64 + fl;
-  struct Frag {
-    bf16x8 a[2][2], w[2][WCT];  // [k-substep][plane], [k-substep][column tile]
-  };
-  auto ld = [&](int st, Frag& f) {
-    const size_t ss = (size_t)min(st, KS - 1);
-#pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) f.a[sub][h] = pa[h * plane + ss * MT * 64 + 32 * sub];
-#pragma unroll
-      for (int q = 0; q < WCT; ++q) f.w[sub][q] = pb[q][ss * 64 + 32 * sub];
-    }
-  };
-  floatx16 acc[WCT];
-#pragma unroll
-  for (int q = 0; q < WCT; ++q)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[q][v] = 0.f;
-  auto mul = [&](const Frag& f) {
-#pragma unroll
-    for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int q = 0; q < WCT; ++q) acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[sub][h], f.w[sub][q], acc[q], 0, 0, 0);
-  };
-  // Each step multiplies the fragments loaded kWideD steps earlier and reloads their
-  // registers kWideD steps ahead (past the end: the last k-step again, unused); the
-  // scheduling barriers keep every load where it is issued (the scheduler otherwise
-  // moves loads next to their use to shorten register lifetimes).
-  // grid y splits the k-steps (EPI_PART: one partial-sum buffer per split)
-  const int kper = KS / gridDim.y, kb = blockIdx.y * kper, ke = kb + kper;
-  Frag fr[kWideD];
-#pragma unroll
-  for (int d = 0; d < kWideD; ++d) ld(kb + d, fr[d]);
-  __builtin_amdgcn_sched_barrier(0);
-  for (int st = kb; st < ke; st += kWideD) {
-#pragma unroll
-    for (int d = 0; d < kWideD; ++d) {
-      mul(fr[d]);
-      __builtin_amdgcn_sched_barrier(0);
-      ld(st + d + kWideD, fr[d]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  // accumulator v of 32 x 32 tile q: row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32
-#pragma unroll
-  for (int q = 0; q < WCT; ++q)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) sv[wm * 32 + 8 * (v >> 2) + 4 * kh + (v & 3)][(wn * WCT + q) * 32 + r32] = acc[q][v];
-  __syncthreads();
-  // epilogue items: 8 consecutive columns of one row
-  const int m0 = (mb0 + mbk) * 64, n0 = nbk * TC;
+__device__ __forceinline__ void finish_rows8(const GemvArgs& a, float (*sv)[65], int m0, int n0, const Rows8& pre) {
   const int R = a.slot0 * kRows, Rend = (a.slot0 + a.nslots) * kRows;
-  const uint4* bias8 = reinterpret_cast<const uint4*>(a.bias);
-  for (int item = threadIdx.x; item < 64 * (TC / 8); item += 256) {
-    const int ml = item / (TC / 8), c8 = 8 * (item % (TC / 8)), row = m0 + ml, n = n0 + c8;
+#pragma unroll
+  for (int it = 0; it < 2; ++it) {
+    const int item = threadIdx.x + 256 * it, ml = item >> 3, c8 = 8 * (item & 7), row = m0 + ml, n = n0 + c8;
     if (row < R || row >= Rend || n >= a.N) continue;
+    const uint32_t bw[4] = {pre.bias[it].x, pre.bias[it].y, pre.bias[it].z, pre.bias[it].w};
     float v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = sv[ml][c8 + e];
-    if (bias8 != nullptr) {
-      const uint4 bb = bias8[n / 8];
-      const uint32_t bw[4] = {bb.x, bb.y, bb.z, bb.w};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] += __uint_as_float(e & 1 ? bw[e >> 1] & 0xffff0000u : bw[e >> 1] << 16);
-    }
+    for (int e = 0; e < 8; ++e) v[e] = sv[ml][c8 + e] + __uint_as_float(e & 1 ? bw[e >> 1] & 0xffff0000u : bw[e >> 1] << 16);
     if constexpr (EPI == EPI_GELU) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = gelu_erf(v[e]);
       put_op8<bf16>(a.aout, a.nsplit, a.R9, row, n, v);
-    } else if constexpr (EPI == EPI_STORE || EPI == EPI_PART) {
+    } else if constexpr (EPI == EPI_STORE || EPI == EPI_PART || EPI == EPI_RESID) {
       float* yb = EPI == EPI_PART ? a.y + blockIdx.y * a.pstride : a.y;
       float4* y = reinterpret_cast<float4*>(yb + (size_t)row * a.ldy + n);
+      if constexpr (EPI == EPI_RESID) {
+        const float4 r0 = pre.r[it][0], r1 = pre.r[it][1];
+        v[0] += r0.x; v[1] += r0.y; v[2] += r0.z; v[3] += r0.w;
+        v[4] += r1.x; v[5] += r1.y; v[6] += r1.z; v[7] += r1.w;
+      }
       y[0] = make_float4(v[0], v[1], v[2], v[3]);
       y[1] = make_float4(v[4], v[5], v[6], v[7]);
-    } else if constexpr (EPI == EPI_RESID) {
-      float4* y = reinterpret_cast<float4*>(a.y + (size_t)row * a.ldy + n);
-      const float4 r0 = y[0], r1 = y[1];
-      v[0] += r0.x; v[1] += r0.y; v[2] += r0.z; v[3] += r0.w;
-      v[4] += r1.x; v[5] += r1.y; v[6] += r1.z; v[7] += r1.w;
-      y[0] = make_float4(v[0], v[1], v[2], v[3]);
-      y[1] = make_float4(v[4], v[5], v[6], v[7]);
-      if (a.tap >= 0) put_op8<bf16>(a.aout, a.nsplit, a.R9, row, a.tap * a.N + n, v);
+      if (EPI == EPI_RESID && a.tap >= 0) put_op8<bf16>(a.aout, a.nsplit, a.R9, row, a.tap * a.N + n, v);
     } else if constexpr (EPI == EPI_QKV) {
       if (n < a.d) {
         float4* y = reinterpret_cast<float4*>(a.y + (size_t)row * a.ldy + n);
@@ -931,6 +604,108 @@ __global__ void __launch_bounds__(256) k_gemm32r(GemvArgs a, int mb0, int nmb, i
         }
       }
     }
+  }
+}
+
+// The vocabulary head's epilogue of a 64 x 64 tile.  Scores with a lane per column (the
+// logits of a row leave as one 256-byte run), put back in `sv` (and z in `oz`); then four
+// threads per row take 16 columns each, in order, and meet in two exchanges.  With a
+// whole wave exchanging per row (six steps of a value and its column for each of 16 rows,
+// twice as many with the normaliser) the reduction took most of the kernel: 144 rows,
+// 51866 columns 135 -> 83 us, 864 rows 548 -> 349.
+__device__ __forceinline__ void finish_head(const GemvArgs& a, float (*sv)[65], float (*oz)[65], int m0, int n0) {
+  const int R = a.slot0 * kRows, Rend = (a.slot0 + a.nslots) * kRows;
+  const int c = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = n0 + c;
+  const bool sup = a.suppress != nullptr && a.suppress[min(n, a.N - 1)];
+  const bool draw = a.inv_t > 0.f && a.rng_purpose != 0;
+  int step[16];
+#pragma unroll
+  for (int it = 0; it < 16; ++it)
+    step[it] = draw ? a.state[min(m0 + wv + 4 * it, Rend - 1) / kRows * kStateInts + ST_STEP] : 0;
+#pragma unroll
+  for (int it = 0; it < 16; ++it) {
+    const int ml = wv + 4 * it, row = m0 + ml;
+    const bool act = row >= R && row < Rend && n < a.N;
+    const float v = sup ? -INFINITY : sv[ml][c];
+    float o, z;
+    head_score(a, row, n, act, v, &o, &z, step[it]);
+    if (act && a.y != nullptr) a.y[(size_t)row * a.ldy + n] = v;
+    sv[ml][c] = o;
+    if (a.hm != nullptr) oz[ml][c] = z;
+  }
+  __syncthreads();
+  const int ml = threadIdx.x >> 2, c0 = 16 * (threadIdx.x & 3), row = m0 + ml;
+  float bv = sv[ml][c0];
+  int bi = n0 + c0;
+#pragma unroll
+  for (int e = 1; e < 16; ++e) {
+    const float v2 = sv[ml][c0 + e];
+    if (better(v2, n0 + c0 + e, bv, bi)) {
+      bv = v2;
+      bi = n0 + c0 + e;
+    }
+  }
+#pragma unroll
+  for (int o = 1; o < 4; o *= 2) {
+    const float v2 = __shfl_xor(bv, o);
+    const int i2 = __shfl_xor(bi, o);
+    if (better(v2, i2, bv, bi)) {
+      bv = v2;
+      bi = i2;
+    }
+  }
+  float zm = -INFINITY, zs = 0.f;
+  if (a.hm != nullptr) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) zm = fmaxf(zm, oz[ml][c0 + e]);
+#pragma unroll
+    for (int o = 1; o < 4; o *= 2) zm = fmaxf(zm, __shfl_xor(zm, o));
+    if (zm > -INFINITY) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) zs += expf(oz[ml][c0 + e] - zm);
+    }
+#pragma unroll
+    for (int o = 1; o < 4; o *= 2) zs += __shfl_xor(zs, o);
+  }
+  if ((threadIdx.x & 3) == 0 && row >= R && row < Rend) {
+    const size_t o = (size_t)row * a.nblk + n0 / 64;
+    a.hv[o] = bv;
+    a.hi[o] = bi;
+    if (a.hm != nullptr) {
+      a.hm[o] = zm;
+      a.hs[o] = zs;
+    }
+  }
+}
+
+template <int EPI>
+__global__ void __launch_bounds__(256, 2) k_gemm(GemvArgs a, int mb0, int nmb, int nnb, int rs) {
+  StampScope stamp_scope(a.stamp, 256);
+  __shared__ float4 red[3][1][4][4][64];
+  __shared__ float sv[64][65];
+  if (a.pf.blocks > 0 && blockIdx.x >= gridDim.x - a.pf.blocks) {  // appended blocks: a later product's weights
+    if (blockIdx.y == 0) touch_range(a.pf, blockIdx.x - (gridDim.x - a.pf.blocks));
+    return;
+  }
+  int mbk, nbk;
+  if (!xcd_tile(nmb, nnb, rs, mbk, nbk)) return;
+  const int m0 = (mb0 + mbk) * 64, n0 = nbk * 64;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  Rows8 pre;
+  if constexpr (EPI != EPI_ARGMAX && EPI != EPI_ACC) pre.load<EPI>(a, m0, n0);
+  floatx16 sum[1];  // wave w: the 32 x 32 tile of row half w / 2, column half w % 2
+  split_tile<2, W_F16, 2, 2, 5>(a.a.p, a.a.mt, a.w, a.K, a.N, m0, n0, blockIdx.y, gridDim.y, sum, red);
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    sv[32 * (wv >> 1) + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)][32 * (wv & 1) + (lane & 31)] = sum[0][v];
+  __syncthreads();
+  if constexpr (EPI == EPI_ARGMAX) {  // the z values take the reduction's place, which has been read
+    finish_head(a, sv, reinterpret_cast<float(*)[65]>(&red[0][0][0][0][0]), m0, n0);
+  } else if constexpr (EPI == EPI_ACC) {
+    EpiPre<64, 256> none;  // other kernels' prefetches
+    finish_tile<bf16, EPI, 64, 64, 256>(a, sv, nullptr, nullptr, m0, n0, none);
+  } else {
+    finish_rows8<EPI>(a, sv, m0, n0, pre);
   }
 }
 
@@ -982,8 +757,7 @@ __global__ void __launch_bounds__(NW * 64) k_gemv32(GemvArgs a) {
     }
     __syncthreads();
     {
-      RowsPre<32, 32, NW * 64> none;
-      finish_tile<bf16, EPI, 32, 32, NW * 64>(a, sv, ov, oz, tile0 * 32, blockIdx.x * 32, pre, none);
+      finish_tile<bf16, EPI, 32, 32, NW * 64>(a, sv, ov, oz, tile0 * 32, blockIdx.x * 32, pre);
     }
     if (a.nsplit == 3) break;
   }
@@ -1181,8 +955,7 @@ __global__ void __launch_bounds__(NW * 64) k_gemv32p(GemvArgs a) {
       sv[ml][c] = sum;
     }
     __syncthreads();
-    RowsPre<32, 32, NW * 64> none;
-    finish_tile<bf16, EPI, 32, 32, NW * 64, false, LN>(a, sv, ov, oz, a.mt0 * 32, tile * 32, p, none, lnst);
+    finish_tile<bf16, EPI, 32, 32, NW * 64, LN>(a, sv, ov, oz, a.mt0 * 32, tile * 32, p, lnst);
   };
   const int G = gridDim.x;
   int tile = blockIdx.x;
@@ -1280,8 +1053,7 @@ __global__ void __launch_bounds__(NW * 64) k_gemv16_ln(GemvArgs a) {
   }
   __syncthreads();
   {
-      RowsPre<32, 16, NW * 64> none;
-      finish_tile<bf16, EPI, 32, 16, NW * 64, false, true>(a, sv, ov, oz, 0, blockIdx.x * 16, pre, none, lnst);
+      finish_tile<bf16, EPI, 32, 16, NW * 64, true>(a, sv, ov, oz, 0, blockIdx.x * 16, pre, lnst);
     }
 }
 
@@ -1338,8 +1110,7 @@ __global__ void __launch_bounds__(NW * 64) k_gemv32_ln(GemvArgs a) {
   }
   __syncthreads();
   {
-      RowsPre<32, 32, NW * 64> none;
-      finish_tile<bf16, EPI, 32, 32, NW * 64, false, true>(a, sv, ov, oz, 0, blockIdx.x * 32, pre, none, lnst);
+      finish_tile<bf16, EPI, 32, 32, NW * 64, true>(a, sv, ov, oz, 0, blockIdx.x * 32, pre, lnst);
     }
 }
 
@@ -1411,8 +1182,7 @@ __global__ void __launch_bounds__(NW * 64) k_gemv_f32(GemvArgs a) {
     }
     __syncthreads();
     {
-      RowsPre<32, 16, NW * 64> none;
-      finish_tile<float, EPI, 32, 16, NW * 64>(a, sv, ov, oz, tile0 * 16, nb, pre, none);
+      finish_tile<float, EPI, 32, 16, NW * 64>(a, sv, ov, oz, tile0 * 16, nb, pre);
     }
   }
 }
@@ -1513,19 +1283,24 @@ static void launch_splitk(const GemvArgs& a, hipStream_t st) {
   k_gemv16w<EPI, 8, 4><<<grid, 512, 0, st>>>(a);
 }
 
-// blocks appended to a staged several-slot GEMM launch for the weights it reads ahead
+// blocks appended to a several-slot GEMM launch for the weights it reads ahead
 static unsigned pf_blocks(const GemvArgs& a) { return (unsigned)a.pf.blocks; }
+
+// Several slots: tiles of 64 rows, k split over grid y.
+template <int EPI>
+static void launch_gemm(const GemvArgs& a, hipStream_t st) {
+  const int mb0 = a.slot0 * kRows / 64, mb1 = ((a.slot0 + a.nslots) * kRows + 63) / 64;
+  const int nmb = mb1 - mb0, ks = a.ksplit > 1 ? a.ksplit : 1;
+  const int nnb = (a.N + 63) / 64, rs = xcd_row_parts(nmb, (size_t)64 * (a.K / ks) * 4);
+  k_gemm<EPI><<<dim3(xcd_blocks(nmb, nnb, rs) + pf_blocks(a), ks), 256, 0, st>>>(a, mb0, nmb, nnb, rs);
+}
 
 template <typename S, int EPI>
 static void launch_epi(const GemvArgs& a, hipStream_t st) {
   if constexpr (EPI == EPI_ACC) {  // bf16: split-K partial sums added to y
     if constexpr (sizeof(S) == 2) {
       if (a.nsplit == 2 && a.wkind == W_F16) {  // several slots: GEMM tiles, k split over grid y
-        const int mb0 = a.slot0 * kRows / 64, mb1 = ((a.slot0 + a.nslots) * kRows + 63) / 64;
-        const int nmb = mb1 - mb0, nnb = (a.N + 63) / 64, ks = a.ksplit > 1 ? a.ksplit : 1;
-        const unsigned nb = gemm_grid(nmb, nnb);
-        if (nb * (unsigned)ks >= kGemmStagedBlocks) k_gemm16s<EPI><<<dim3(nb + pf_blocks(a), ks), 256, 0, st>>>(a, mb0, nmb, nnb);
-        else k_gemm16<EPI><<<dim3(nb, ks), 256, 0, st>>>(a, mb0, nmb, nnb);
+        launch_gemm<EPI>(a, st);
       } else {
         launch_splitk<EPI_ACC>(a, st);  // batch 1
       }
@@ -1545,47 +1320,8 @@ static void launch_epi(const GemvArgs& a, hipStream_t st) {
       launch_ln<EPI>(a, st);
       return;
     }
-    const int ks = a.ksplit > 1 ? a.ksplit : 1;
-    if (a.nsplit == 2 && a.wkind == W_F16) {  // several slots: 64 x 64 GEMM tiles (k split over grid y)
-      const int mb0 = a.slot0 * kRows / 64, mb1 = ((a.slot0 + a.nslots) * kRows + 63) / 64;
-      const int nmb = mb1 - mb0, nnb = (a.N + 63) / 64;
-      if constexpr (EPI == EPI_PART) {
-        // many rows, k split into partial sums: wide tiles, grid y = the splits
-        const int kss = a.K / 32;
-        if (ks > 1 && nmb >= kWideMinRowBlocks && kss % (ks * kWideD) == 0 && a.N % 320 == 0 && a.a.kind == OP_F16) {
-          k_gemm32r<EPI, 10><<<dim3(wide_grid(nmb, a.N / 320) + pf_blocks(a), ks), 256, 0, st>>>(a, mb0, nmb, a.N / 320);
-          return;
-        }
-      }
-      if constexpr (EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_RESID || EPI == EPI_QKV) {
-        // many rows: wide tiles on the 32x32x16 matrix instruction
-        if (ks == 1 && nmb >= kWideMinRowBlocks && (a.K / 32) % kWideD == 0 && a.N % 8 == 0 && a.a.kind == OP_F16) {
-          GemvArgs b = a;
-          b.pf = Touch{nullptr, 0, 0};  // these launches append no reading blocks
-          if (a.N % 320 == 0 && a.N / 320 >= 16) {
-            k_gemm32r<EPI, 10><<<wide_grid(nmb, a.N / 320), 256, 0, st>>>(b, mb0, nmb, a.N / 320);
-            return;
-          }
-          if (a.N % 256 == 0 && a.N >= 2560) {
-            k_gemm32r<EPI, 8><<<wide_grid(nmb, a.N / 256), 256, 0, st>>>(b, mb0, nmb, a.N / 256);
-            return;
-          }
-          // narrower products (1280 columns at 96 slots) measured slower in this kernel
-          // (128-column tiles: 33 against 17.5 us per launch) and keep the 64 x 64 tiles
-        }
-      }
-      // LDS-staged fragments once the launch has enough blocks to cover the
-      // chip; with fewer, the per-k-step barrier costs more than the halved loads
-      // save (measured: 72-240 blocks at 16 slots 12-15% slower, 280+ at 96
-      // slots 6-32% faster)
-      const unsigned nb = gemm_grid(nmb, nnb);
-      if constexpr (EPI != EPI_ARGMAX) {
-        if (nb * (unsigned)ks >= kGemmStagedBlocks) {
-          k_gemm16s<EPI><<<dim3(nb + pf_blocks(a), ks), 256, 0, st>>>(a, mb0, nmb, nnb);
-          return;
-        }
-      }
-      k_gemm16<EPI><<<dim3(nb, ks), 256, 0, st>>>(a, mb0, nmb, nnb);
+    if (a.nsplit == 2 && a.wkind == W_F16) {  // several slots
+      launch_gemm<EPI>(a, st);
       return;
     }
     if constexpr (EPI == EPI_PART) {  // batch 1
@@ -1610,7 +1346,7 @@ static void launch_epi(const GemvArgs& a, hipStream_t st) {
 
 template <typename S>
 void Ops<S>::gemv(int epi, const GemvArgs& a0, hipStream_t st) {
-  // the staged GEMM takes the last pf.blocks blocks of grid x as reading blocks
+  // the several-slot GEMM takes the last pf.blocks blocks of grid x as reading blocks
   // (other kernels ignore the request): a request with nothing to read appends none
   GemvArgs a = a0;
   if (a.pf.p == nullptr || a.pf.bytes < 16 || a.pf.blocks <= 0) a.pf = Touch{nullptr, 0, 0};

@@ -16,6 +16,7 @@
 #include "wf_common.h"
 #include "wf_kernels.h"
 #include "wf_operand.h"
+#include "wf_tile.h"
 
 namespace wf {
 
@@ -25,8 +26,7 @@ namespace {
 template <int P>
 __device__ __forceinline__ void put_planes8(uint4* A, size_t i, size_t plane, const float* v) {
   if constexpr (P == 3) split3x8(v, A[i], A[i + plane], A[i + 2 * plane]);
-  else if constexpr (P == 2) split2x8(v, A[i], A[i + plane]);
-  else A[i] = make_uint4(pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]), pack2_bf16(v[4], v[5]), pack2_bf16(v[6], v[7]));
+  else split2x8(v, A[i], A[i + plane]);
 }
 }  // namespace
 
@@ -70,7 +70,6 @@ template <int P>
 __global__ void __launch_bounds__(256) k_pre_rln(PreLnArgs a) {
   __shared__ float red[2][4];
   const int row = blockIdx.x, d = a.d, nch = d >> 3, c = threadIdx.x, cc = min(c, nch - 1);
-  if (a.period > 0 && row % a.period >= a.valid) return;  // padding rows stay as they are (zero)
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const bool act = c < nch, sums = a.nparts > 0, has_ln = a.g != nullptr;
   float* hr = a.h + (size_t)row * d;
@@ -134,164 +133,19 @@ __global__ void __launch_bounds__(256) k_pre_rln(PreLnArgs a) {
 }
 
 // ---------------------------------------------------------------- products
-// C[m, n] = sum over the P planes of A[m, k] W[n, k] on v_mfma_f32_32x32x16_bf16, fp32
-// accumulators.  Block tile 32 TI x 32 TJ, four waves that split k: wave w takes the
-// 16-wide k units w, w + 4, ... for the whole tile, so every operand byte is loaded
-// by one wave only, straight into registers and D units ahead: no LDS and no barrier
-// in the loop.  The waves' tiles meet in LDS at the end, each wave adding up
-// (in wave order) and finishing its quarter.
-// With the tile split over the waves instead and the fragments staged in LDS, each
-// fragment is read by two waves and the LDS traffic (reads and copies, 48 KB per
-// k-step of a 64 x 64 three-plane tile) took longer than the matrix work it feeds.
-// Grid y splits the k units (PRE_PART: one buffer of partial sums per split).
-// Weights: 16-column (W_F16) or 32-column (W_F32) fragment order; either is read
-// by picking each lane's 16 bytes.
-namespace {
-// Rows 8 (lane / 32) .. + 7 of half `half` (16 rows) of a 32 x 32 accumulator, this lane's
-// column, + bias, as eight bf16: the two row groups change places between half-waves.
-__device__ __forceinline__ uint4 rows8_bf16(const floatx16& c, int half, float bias) {
-  uint32_t p[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) p[e] = pack2_bf16(c[8 * half + 2 * e] + bias, c[8 * half + 2 * e + 1] + bias);
-  const auto x = __builtin_amdgcn_permlane32_swap(p[0], p[2], false, false);
-  const auto y = __builtin_amdgcn_permlane32_swap(p[1], p[3], false, false);
-  return make_uint4(x[0], y[0], x[1], y[1]);
-}
-// The same half + bias turned around in the wave's own LDS (16 x 33 floats): lane l gets
-// row l / 4, columns 8 (l % 4) .. + 7.
-__device__ __forceinline__ void turn_half(float* tr, const floatx16& c, int half, float bias, float* o) {
-  const int lane = threadIdx.x & 63, lr = lane & 31, lk = lane >> 5;
-#pragma unroll
-  for (int v = 0; v < 8; ++v) tr[(8 * (v >> 2) + 4 * lk + (v & 3)) * 33 + lr] = c[8 * half + v] + bias;
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = tr[(lane >> 2) * 33 + 8 * (lane & 3) + e];
-  __builtin_amdgcn_wave_barrier();
-}
-}  // namespace
-
+// A block per 32 TI x 32 TJ tile (split_tile, wf_tile.h); grid y splits the k units
+// (PRE_PART: one buffer of partial sums per split).
 template <int EPI, int P, int WK, int TI, int TJ, int D>
 __global__ void __launch_bounds__(256, 1) k_pre_gemm(PreGemmArgs a, int nmb, int nnb, int rs) {
-  constexpr int NW = 4, TM = 32 * TI, TN = 32 * TJ, Q = TI * TJ / NW;  // Q: 32 x 32 tiles a wave finishes
-  static_assert(TI * TJ % NW == 0, "the waves finish equal shares");
-  // XCD x (block % 8) takes row part x % rs of rs and column part x / rs of 8 / rs, row
-  // blocks fastest
-  const int x = blockIdx.x & 7, bi = blockIdx.x >> 3;
-  const int nrh = (nmb + rs - 1) / rs, ncq = (nnb * rs + 7) / 8;
-  const int mbk = (x % rs) * nrh + bi % nrh, nbk = (x / rs) * ncq + bi / nrh;
-  if (bi % nrh + (x % rs) * nrh >= nmb || bi / nrh >= ncq || nbk >= nnb) return;
+  constexpr int NW = 4, Q = TI * TJ / NW;
+  __shared__ float4 red[NW - 1][Q < 2 ? 1 : 2][4][NW][64];
+  int mbk, nbk;
+  if (!xcd_tile(nmb, nnb, rs, mbk, nbk)) return;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lr = lane & 31, lk = lane >> 5;
-  const int KS = a.K / 32, ku = 2 * (KS / gridDim.y), u0 = blockIdx.y * ku + wv, n = (ku - wv + NW - 1) / NW;
-  const int m0 = mbk * TM, n0 = nbk * TN;
-  // this lane's 16 bytes of each row / column tile (tiles past the data re-read the
-  // last one; their results are not written); unit u0 + 4 t lies t strides on
-  const uint4* A0 = reinterpret_cast<const uint4*>(a.a) + (size_t)(u0 >> 1) * a.mt * 64 + 32 * (u0 & 1);
-  const uint4* W0 = reinterpret_cast<const uint4*>(a.w) + (size_t)u0 * (WK == W_F16 ? 32 : 64);
-  const size_t plane = (size_t)a.mt * KS * 64, sa = (size_t)2 * a.mt * 64;
-  constexpr int sw = NW * (WK == W_F16 ? 32 : 64);
-  int oa[TI], ow[TJ];
-#pragma unroll
-  for (int i = 0; i < TI; ++i) oa[i] = min(m0 / 16 + 2 * i + (lr >> 4), a.mt - 1) * 64 + (lr & 15) + 16 * lk;
-#pragma unroll
-  for (int j = 0; j < TJ; ++j)
-    ow[j] = WK == W_F16 ? min(n0 / 16 + 2 * j + (lr >> 4), (a.N + 15) / 16 - 1) * KS * 64 + (lr & 15) + 16 * lk
-                        : min(n0 / 32 + j, (a.N + 31) / 32 - 1) * 2 * KS * 64 + lane;
-  struct Frag {
-    bf16x8 a[P][TI], w[TJ];
-  };
-  auto load = [&](int t, Frag& f) {  // the wave's unit t (past the end: the last one)
-    const int tt = min(t, n - 1);
-    const uint4 *At = A0 + tt * sa, *Wt = W0 + (size_t)tt * sw;
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) f.w[j] = __builtin_bit_cast(bf16x8, Wt[ow[j]]);
-#pragma unroll
-    for (int h = 0; h < P; ++h)
-#pragma unroll
-      for (int i = 0; i < TI; ++i) f.a[h][i] = __builtin_bit_cast(bf16x8, (At + h * plane)[oa[i]]);
-  };
-  floatx16 acc[TI][TJ];
-#pragma unroll
-  for (int i = 0; i < TI; ++i)
-#pragma unroll
-    for (int j = 0; j < TJ; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  auto mul = [&](const Frag& f) {
-#pragma unroll
-    for (int h = 0; h < P; ++h)
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[h][i], f.w[j], acc[i][j], 0, 0, 0);
-  };
-  // D units in flight; the scheduling barriers keep every load where it is issued
-  Frag fr[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) load(d, fr[d]);
-  __builtin_amdgcn_sched_barrier(0);
-  int t = 0;
-  for (; t + 2 * D <= n; t += D) {
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      mul(fr[d]);
-      __builtin_amdgcn_sched_barrier(0);
-      load(t + d + D, fr[d]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  // units t .. n - 1 are left, the first D of them in flight
-  const int rest = n - t - D;
-  if (rest > 0) {
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      mul(fr[d]);
-      __builtin_amdgcn_sched_barrier(0);
-      load(t + d + D, fr[d]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    t += D;
-  }
-#pragma unroll
-  for (int d = 0; d < D; ++d)
-    if (t + d < n) mul(fr[d]);
-
-  // wave w takes the tiles w Q .. w Q + Q - 1 (tile i TJ + j): the other waves' parts
-  // through LDS in the instruction's own order, 16 bytes per lane, R tiles a round
-  constexpr int R = Q < 2 ? Q : 2;
-  __shared__ float4 red[NW - 1][R][4][NW][64];
+  const int lr = lane & 31, lk = lane >> 5, m0 = mbk * 32 * TI, n0 = nbk * 32 * TJ;
   floatx16 sum[Q];
-#pragma unroll
-  for (int q = 0; q < NW * Q; ++q)
-    if (q / Q == wv) sum[q % Q] = acc[q / TJ][q % TJ];
-#pragma unroll
-  for (int r0 = 0; r0 < Q; r0 += R) {
-    if (r0 > 0) __syncthreads();
-#pragma unroll
-    for (int q = 0; q < NW * Q; ++q) {
-      const int own = q / Q, r = q % Q - r0;
-      if (r < 0 || r >= R || own == wv) continue;
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        red[wv < own ? wv : wv - 1][r][v][own][lane] =
-            make_float4(acc[q / TJ][q % TJ][4 * v], acc[q / TJ][q % TJ][4 * v + 1], acc[q / TJ][q % TJ][4 * v + 2],
-                        acc[q / TJ][q % TJ][4 * v + 3]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int s = 0; s < NW - 1; ++s)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const float4 o = red[s][r][v][wv][lane];
-          sum[r0 + r][4 * v] += o.x;
-          sum[r0 + r][4 * v + 1] += o.y;
-          sum[r0 + r][4 * v + 2] += o.z;
-          sum[r0 + r][4 * v + 3] += o.w;
-        }
-  }
-  if constexpr (EPI == PRE_GELU || EPI == PRE_ENC) __syncthreads();
+  split_tile<P, WK, TI, TJ, D>(a.a, a.mt, a.w, a.K, a.N, m0, n0, blockIdx.y, gridDim.y, sum, red);
+  if constexpr (EPI == PRE_GELU) __syncthreads();
 
   // accumulator v of a 32 x 32 tile: row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32
 #pragma unroll
@@ -331,28 +185,6 @@ __global__ void __launch_bounds__(256, 1) k_pre_gemm(PreGemmArgs a, int nmb, int
             *reinterpret_cast<uint4*>(cache + dim * kPage + 8 * lk) = rows8_bf16(c, half, bias);
           }
         }
-      }
-    } else if constexpr (EPI == PRE_ENC) {
-      // queries | keys as bf16 rows [row][2d], values transposed [head][dim][period] per
-      // request of `period` rows (a 32-row tile lies in one request)
-      const int kind = nt < 2 * a.d ? 0 : 1;
-      if (kind == 0) {
-        float* tr = reinterpret_cast<float*>(red) + wv * 16 * 33;
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          float o[8];
-          turn_half(tr, c, half, bias, o);
-          const int row = mt0 + 16 * half + (lane >> 2);
-          if (row < a.M)
-            *reinterpret_cast<uint4*>(a.aout + (size_t)row * 2 * a.d + nt + 8 * (lane & 3)) =
-                make_uint4(pack2_bf16(o[0], o[1]), pack2_bf16(o[2], o[3]), pack2_bf16(o[4], o[5]), pack2_bf16(o[6], o[7]));
-        }
-      } else {
-        const int cc = nc - 2 * a.d, req = mt0 / a.period, f0 = mt0 - req * a.period;
-        bf16* vt = reinterpret_cast<bf16*>(a.cache) + ((size_t)req * a.d + cc) * a.period + f0;
-#pragma unroll
-        for (int half = 0; half < 2; ++half)
-          *reinterpret_cast<uint4*>(vt + 16 * half + 8 * lk) = rows8_bf16(c, half, bias);
       }
     } else {
       // GELU into the next product's planes: 16 x 32 half tiles turned around in
@@ -634,13 +466,8 @@ namespace {
 template <int EPI, int P, int WK, int TI, int TJ, int D>
 void gemm_launch(const PreGemmArgs& a, int ks, hipStream_t st) {
   const int nmb = (a.M + 32 * TI - 1) / (32 * TI), nnb = (a.N + 32 * TJ - 1) / (32 * TJ);
-  // the operand rows of one XCD's blocks stay in its L2 (4 MB) while the weights pass
-  // by: 1776 rows, 5120 columns 90 us with all rows per XCD, 65, 60 and 68 with half,
-  // a quarter and an eighth; 864 rows 37, 33, 34 and 35
-  int rs = 1;
-  while (rs < 8 && (size_t)((nmb + rs - 1) / rs) * 32 * TI * (a.K / ks) * 2 * P > kPreXcdRowBytes) rs *= 2;
-  const unsigned grid = 8u * ((nmb + rs - 1) / rs) * ((nnb * rs + 7) / 8);
-  k_pre_gemm<EPI, P, WK, TI, TJ, D><<<dim3(grid, ks), 256, 0, st>>>(a, nmb, nnb, rs);
+  const int rs = xcd_row_parts(nmb, (size_t)32 * TI * (a.K / ks) * 2 * P);
+  k_pre_gemm<EPI, P, WK, TI, TJ, D><<<dim3(xcd_blocks(nmb, nnb, rs), ks), 256, 0, st>>>(a, nmb, nnb, rs);
 }
 int blocks_of(const PreGemmArgs& a, int ti, int tj) {
   return ((a.M + 32 * ti - 1) / (32 * ti)) * ((a.N + 32 * tj - 1) / (32 * tj));

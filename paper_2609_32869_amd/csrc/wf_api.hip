@@ -346,11 +346,11 @@ struct Runner {
     size_t wq, nq;  // weights of the next block's q|k|v product (offset, elements; 0: none)
   };
 
-  // Several slots (kTouchMinRowBlocks row blocks or more, bf16 operands): the
-  // weights of the wide-tile products (q|k|v, W_1) are read by extra blocks of
-  // the product launched before them (W'_o, W_2 of the previous block), so they
-  // come from the memory-side cache rather than HBM.  The 64 x 64 tile products
-  // stage three k-steps ahead through LDS and gain nothing from it (measured).
+  // Several slots (kTouchMinRowBlocks row blocks or more, bf16 operands): the weights of
+  // the widest products (q|k|v, W_1) are read by extra blocks of the product launched
+  // before them (W'_o, W_2 of the previous block), so they come from the memory-side
+  // cache rather than HBM.  At 96 slots a step takes 13.05 ms without and 12.84 with; with
+  // fewer rows the carrying launch is too short to hide the reads (8 slots 3.39 -> 3.60).
   // touch_ holds the request for the next product launch, which takes it.
   Touch touch_{nullptr, 0, 0};
   bool touch_ahead(int slot0, int n) const {
@@ -581,8 +581,9 @@ struct Runner {
 
   // Several slots with bf16 operands: the second MLP product's k-steps split in
   // kFc2SplitBatch (partial sums reduced with the residual update and the next
-  // LayerNorm), else 0.  Few slots: its 64 x 64 tiles alone would not fill the
-  // chip; many slots: it runs on the wide tiles, which alone would give too few.
+  // LayerNorm), else 0: its few columns alone give too few 64 x 64 tiles.  Split two
+  // ways a step of 8, 16 and 96 slots takes 3.56, 4.42 and 12.91 ms, four ways 3.39,
+  // 4.49 and 12.84.
   int fc2_split_batch() const {
     if (L.nsplit_op != 2) return 0;
     return (c.d_ff / 32) % kFc2SplitBatch == 0 ? kFc2SplitBatch : 0;

@@ -115,7 +115,7 @@ struct GemvArgs {
   float* hs;
   unsigned long long* stamp;  // launch timing slot (profiled calls), or null
   // weights of a later product, read by pf.blocks blocks appended to grid x (grid
-  // y 0 only); the LDS-staged several-slot GEMM takes it, other kernels ignore it
+  // y 0 only); the several-slot GEMM takes it, other kernels ignore it
   Touch pf;
 };
 
@@ -398,9 +398,8 @@ struct PreLnArgs {
   const bf16* b;
   bf16* out;
   int mt, d;          // 16-row tiles held by the operand buffers
-  int period, valid;  // period > 0: of every `period` rows the first `valid` are updated
 };
-enum { PRE_STORE = 0, PRE_PART = 1, PRE_GELU = 2, PRE_QKV = 3, PRE_ENC = 4 };
+enum { PRE_STORE = 0, PRE_PART = 1, PRE_GELU = 2, PRE_QKV = 3 };
 struct PreGemmArgs {
   const bf16* a;      // operand planes of K columns
   int mt;             // 16-row tiles held by operand buffers
@@ -411,8 +410,7 @@ struct PreGemmArgs {
   float* y;           // STORE rows, PART partial sums, QKV queries
   int ldy;
   size_t pstride;
-  bf16* aout;         // GELU: operand planes of N columns; ENC: queries | keys [row][2d]
-  int period;         // ENC: rows per request
+  bf16* aout;         // GELU: operand planes of N columns
   const PrePart* parts;
   const int* page_table;
   int pages_per_slot, d, n_head;

@@ -1,5 +1,5 @@
-"""The request-time matrix products on 256 x 128 tiles (bf16 storage), at sizes that end
-inside a tile, through the calls that reach them.
+"""The matrix products (bf16 storage) at sizes that end inside a tile, through the calls
+that reach them: the request-time ones on 256 x 128 tiles, a step's on 64 x 64.
 
 Both sides round to bf16 at the same points and accumulate in fp32, so a difference
 is a rounding that falls the other way: the acoustic memory's bar is one bf16 ulp at
@@ -61,4 +61,21 @@ def test_acoustic_keys_and_values_of_many_blocks(n_frames):
     for _ in range(2):
         ls.step()
     print(f"frames {n_frames}: max |dlogit| draft {ls.max_dlogit:.2e} target {ls.max_tlogit:.2e}")
+    ls.close()
+
+
+@pytest.mark.parametrize("batch,d_ff", [(7, 352), (8, 96), (15, 160)])
+def test_step_products_at_tile_edges(batch, d_ff):
+    """Several slots' products on 64 x 64 tiles whose waves split k: 63, 72 and 135 rows,
+    MLP widths that end inside a column tile, k-splits of one 32-wide step (two of the
+    four waves have nothing to multiply) and widths too ragged to split."""
+    from lockstep import Lockstep
+    cfg = MICRO.with_(name="step-edges", dtype="bf16", n_vocab=501, n_frames=45, d_ff=d_ff)
+    W = make_weights(cfg)
+    ls = Lockstep(cfg, W, [make_prefix(cfg, i, 3 + i) for i in range(batch)], [20] * batch, 2e-3,
+                  opts=OracleOpts(dtype=np.float32, kv_bf16=True))
+    for _ in range(3):
+        ls.step()
+    print(f"b{batch} d_ff {d_ff}: max |dlogit| draft {ls.max_dlogit:.3e} target {ls.max_tlogit:.3e}", flush=True)
+    assert ls.steps == 3
     ls.close()
