@@ -33,16 +33,22 @@ __device__ __forceinline__ float block_max(float v, float* red) {
 }  // namespace
 
 // One block per frame f of one request: the frame's n_fft samples (reflect-padded
-// signal, periodic Hann window), their power spectrum by a direct DFT in fp64,
-// the mel filterbank (each filter summed over its nonzero bins) and log10 of
-// max(mel, 1e-10), written to logmel[f][m]; the request's maximum goes to *gmax
-// as an order-preserving int.
-__global__ void __launch_bounds__(256) k_logmel(LogmelArgs a) {
+// signal, periodic Hann window), their power spectrum in fp64, the mel filterbank (each
+// filter summed over its nonzero bins) and log10 of max(mel, 1e-10), written to
+// logmel[f][m]; the request's maximum goes to *gmax as an order-preserving int.
+// The transform in two stages (Cooley and Tukey): N = A B, sample B n1 + n2, bin k:
+//   S[k mod A][n2] = sum over n1 of x[B n1 + n2] exp(-2 pi i B n1 k / N)
+//   X[k] = sum over n2 of S[k mod A][n2] exp(-2 pi i n2 k / N),
+// A the divisor of N next below sqrt(N).  The samples are real, so the rows S[A - j] are
+// the conjugates of S[j].  Bound by LDS latency along the sums: A + B terms in a row
+// instead of N (20 + 20 against 400; four requests of 3000 frames, 128 filters 399 -> 148 us).
+__global__ void __launch_bounds__(256) k_logmel(LogmelArgs a, int A) {
   __shared__ double xw[kMaxFft];
-  __shared__ double tw[2 * kMaxFft];
+  __shared__ __align__(16) double tw[2 * kMaxFft];
   __shared__ double pw[kMaxFft / 2 + 1];
+  __shared__ double2 S[kMaxFft + 2];  // A / 2 + 1 rows of B + 1 values: the most for A = 2 (N is even)
   __shared__ float red[4];
-  const int f = blockIdx.x, N = a.n_fft, nb = N / 2 + 1;
+  const int f = blockIdx.x, N = a.n_fft, nb = N / 2 + 1, B = N / A;
   a.audio += (size_t)blockIdx.y * a.n_samples;
   a.logmel += (size_t)blockIdx.y * a.n_frames * a.n_mels;
   a.gmax += blockIdx.y;
@@ -55,12 +61,35 @@ __global__ void __launch_bounds__(256) k_logmel(LogmelArgs a) {
     tw[2 * i + 1] = a.twiddle[2 * i + 1];
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < nb; k += blockDim.x) {
+  const double2* tw2 = reinterpret_cast<const double2*>(tw);
+  for (int j = threadIdx.x; j < (A / 2 + 1) * B; j += blockDim.x) {
+    const int k1 = j / B, n2 = j - k1 * B, step = B * k1;
     double re = 0.0, im = 0.0;
     int idx = 0;
-    for (int i = 0; i < N; ++i) {  // exp(-2 pi i k i / N): index (k i) mod N of the table
-      re = fma(xw[i], tw[2 * idx], re);
-      im = fma(xw[i], tw[2 * idx + 1], im);
+#pragma unroll 4
+    for (int n1 = 0; n1 < A; ++n1) {
+      const double x = xw[B * n1 + n2];
+      const double2 w = tw2[idx];
+      re = fma(x, w.x, re);
+      im = fma(x, w.y, im);
+      idx += step;
+      if (idx >= N) idx -= N;
+    }
+    S[k1 * (B + 1) + n2] = make_double2(re, im);
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < nb; k += blockDim.x) {
+    const int k1 = k % A;
+    const bool conj = k1 > A / 2;
+    const double2* Sr = S + (conj ? A - k1 : k1) * (B + 1);
+    double re = 0.0, im = 0.0;
+    int idx = 0;
+#pragma unroll 4
+    for (int n2 = 0; n2 < B; ++n2) {
+      const double2 v = Sr[n2], w = tw2[idx];
+      const double y = conj ? -v.y : v.y;
+      re = fma(v.x, w.x, fma(-y, w.y, re));
+      im = fma(v.x, w.y, fma(y, w.x, im));
       idx += k;
       if (idx >= N) idx -= N;
     }
@@ -71,6 +100,7 @@ __global__ void __launch_bounds__(256) k_logmel(LogmelArgs a) {
   for (int m = threadIdx.x; m < a.n_mels; m += blockDim.x) {
     const int lo = a.fband[2 * m], hi = a.fband[2 * m + 1];
     double s = 0.0;
+#pragma unroll 8
     for (int k = lo; k < hi; ++k) s = fma(a.filters[(size_t)m * nb + k], pw[k], s);
     const float lg = (float)log10(fmax(s, 1e-10));
     a.logmel[(size_t)f * a.n_mels + m] = lg;
@@ -338,7 +368,10 @@ void enc_attention(const EncAttnArgs& a, int n_head, hipStream_t st) {
 
 void logmel(const LogmelArgs& a, hipStream_t st) {
   k_logmel_init<<<1, 64, 0, st>>>(a.gmax, a.nreq);
-  k_logmel<<<dim3(a.n_frames, a.nreq), 256, 0, st>>>(a);
+  int fft_a = 1;
+  for (int i = 2; i * i <= a.n_fft; ++i)
+    if (a.n_fft % i == 0) fft_a = i;
+  k_logmel<<<dim3(a.n_frames, a.nreq), 256, 0, st>>>(a, fft_a);
   const size_t total = (size_t)a.n_frames * a.ld1;
   k_logmel_rows<<<dim3((unsigned)std::min<size_t>((total + 255) / 256, 4096), a.nreq), 256, 0, st>>>(a);
 }

@@ -79,3 +79,20 @@ def test_step_products_at_tile_edges(batch, d_ff):
     print(f"b{batch} d_ff {d_ff}: max |dlogit| draft {ls.max_dlogit:.3e} target {ls.max_tlogit:.3e}", flush=True)
     assert ls.steps == 3
     ls.close()
+
+
+@pytest.mark.parametrize("n_fft", [6, 162, 250, 254, 506, 512])
+def test_frontend_window_lengths(n_fft):
+    """The two-stage transform at 2 x 3, 9 x 18, 10 x 25, 2 x 127, 22 x 23 and 16 x 32: an odd
+    first factor, the longest second one and the longest window, against numpy's rfft (fp64
+    on both sides; the bar is the stored fp32 log10 value's)."""
+    from oracle.encoder import log_mel
+    from paper_2609_32869_amd import WhisperEncoder
+    ecfg = MICRO_ENC.with_(name="enc-fft", n_fft=n_fft)
+    W = make_encoder_weights(ecfg)
+    enc = WhisperEncoder.from_host(ecfg, [W.values[k] for k, _ in W.order])
+    x = make_audio(ecfg, 0)
+    got = enc.logmel(torch.from_numpy(x).cuda()).cpu().numpy()
+    enc.close()
+    want = log_mel(x, ecfg.n_mels, n_fft)
+    np.testing.assert_allclose(got, want[:, :got.shape[1]], rtol=0, atol=1e-5)
