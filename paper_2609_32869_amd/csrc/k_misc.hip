@@ -690,78 +690,75 @@ void accept_sample(const SampleArgs& a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------- encode: cross K/V
-// C[f, n] = sum_k A[f, k] W[n, k] + b[n] for the 2d key/value columns of one
-// block, written to the per-head cross cache: keys frame-major [head][frame][64];
-// values frame-major too, or transposed in 256-frame pieces
-// [head][frame / 256][dim][256] (vt_frames frames per head) when vt_frames > 0
-// (bf16 storage, read by the matrix-core cross-attention).  64x64 tiles, fp32
-// accumulation.
-template <typename S>
+// C[f, n] = sum_k A[f, k] W[n, k] + b[n] for the 2d key/value columns of every block and
+// slot (grid z), fp32, written to the per-head cross cache [k | v][head][frame][64].
+// 64 x 64 tiles on v_mfma_f32_32x32x2f32 (exact fp32 products and sums), a 32 x 32
+// quadrant per wave; k-steps of 32 through LDS, the next one's loads in flight while
+// this one multiplies.  Lane half h reads k 8 j + 4 h .. + 3 as one 16-byte run; operand
+// and weight rows agree on that order.  Bound by the matrix units: 64 cycles per 32 x
+// 32 x 2.  With vector FMAs (4 x 4 per thread, k-steps of 16) and a launch per block
+// and slot, d 384, 1500 frames, 6 blocks, 3 slots: 18 x 48 us; here 178 us in
+// two launches.
+// VEC: the memory's rows are 16-byte aligned (a caller's buffer need not be).
+constexpr int kXkvK = 32;
+template <bool VEC>
 __global__ void __launch_bounds__(256) k_gemm_xkv(XkvArgs a) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
-  const S* A = reinterpret_cast<const S*>(a.mem);
-  const S* W = reinterpret_cast<const S*>(a.w);
-  const S* bias = reinterpret_cast<const S*>(a.bias);
-  const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int K = a.d, M = a.n_frames, N = 2 * a.d;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int t = threadIdx.x; t < 64 * 16; t += 256) {
-      const int mm = t >> 4, kk = t & 15;
-      As[kk][mm] = (m0 + mm < M) ? to_f(A[(size_t)(m0 + mm) * K + k0 + kk]) : 0.f;
-      Bs[kk][mm] = to_f(W[(size_t)(n0 + mm) * K + k0 + kk]);
-    }
+  __shared__ float As[2][64][kXkvK + 4], Ws[2][64][kXkvK + 4];
+  const int layer = blockIdx.z % a.nlayer, slot = blockIdx.z / a.nlayer;
+  const float* A = a.mem + slot * a.smem;
+  const float* W = a.w + layer * a.sw;
+  const float* bias = a.bias + layer * a.sbias;
+  float* out = a.out + layer * a.sout_layer + slot * a.sout_slot;
+  const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64, K = a.d, M = a.n_frames;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, r32 = lane & 31, half = lane >> 5;
+  const int wm = 32 * (wv >> 1), wn = 32 * (wv & 1);
+  // a thread stages 4 floats of rows t / 8 and t / 8 + 32 of both (rows past the frames
+  // re-read the last one, their results are not written)
+  const int lrow = threadIdx.x >> 3, lk = 4 * (threadIdx.x & 7);
+  const float* pa0 = A + (size_t)min(m0 + lrow, M - 1) * K + lk;
+  const float* pa1 = A + (size_t)min(m0 + lrow + 32, M - 1) * K + lk;
+  const float* pw0 = W + (size_t)(n0 + lrow) * K + lk;
+  const float* pw1 = pw0 + (size_t)32 * K;
+  auto mem4 = [](const float* p) {
+    if constexpr (VEC) return *reinterpret_cast<const float4*>(p);
+    else return make_float4(p[0], p[1], p[2], p[3]);
+  };
+  floatx16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  float4 a0 = mem4(pa0), a1 = mem4(pa1);
+  float4 w0 = *reinterpret_cast<const float4*>(pw0), w1 = *reinterpret_cast<const float4*>(pw1);
+  for (int k0 = 0, s = 0; k0 < K; k0 += kXkvK, s ^= 1) {
+    // stage s was read two steps ago, before the last barrier
+    *reinterpret_cast<float4*>(&As[s][lrow][lk]) = a0;
+    *reinterpret_cast<float4*>(&As[s][lrow + 32][lk]) = a1;
+    *reinterpret_cast<float4*>(&Ws[s][lrow][lk]) = w0;
+    *reinterpret_cast<float4*>(&Ws[s][lrow + 32][lk]) = w1;
     __syncthreads();
+    const int kn = min(k0 + kXkvK, K - kXkvK);  // past the end: the last step again, unused
+    a0 = mem4(pa0 + kn);
+    a1 = mem4(pa1 + kn);
+    w0 = *reinterpret_cast<const float4*>(pw0 + kn);
+    w1 = *reinterpret_cast<const float4*>(pw1 + kn);
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
+    for (int j = 0; j < kXkvK; j += 8) {
+      const float4 x = *reinterpret_cast<const float4*>(&As[s][wm + r32][j + 4 * half]);
+      const float4 w = *reinterpret_cast<const float4*>(&Ws[s][wn + r32][j + 4 * half]);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, w.x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, w.y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, w.z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, w.w, acc, 0, 0, 0);
     }
-    __syncthreads();
   }
-  S* out = reinterpret_cast<S*>(a.out);
-  if (a.vt_frames > 0 && n0 >= a.d) {
-    // value columns of one head, stored transposed in 256-frame pieces
-    // [frame / 256][dim][256]: the tile goes through LDS so that consecutive
-    // threads write consecutive frames; frames from n_frames to vt_frames are
-    // written as zeros
-    __shared__ float Ct[64][65];
+  // accumulator v: row 8 (v / 4) + 4 half + v % 4, column r32; the tile's columns are one head's
+  const int kv = n0 >= a.d, head = (n0 - kv * a.d) >> 6;
+  const float bb = bias[n0 + wn + r32];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) Ct[tx * 4 + j][ty * 4 + i] = acc[i][j] + to_f(bias[n0 + tx * 4 + j]);
-    __syncthreads();
-    const int head = (n0 - a.d) >> 6;
-    S* vt = out + (size_t)a.n_head * M * kHeadDim + (size_t)head * kHeadDim * a.vt_frames;
-    for (int t = threadIdx.x; t < 64 * 64; t += 256) {
-      const int dim = t >> 6, fl = t & 63, f = m0 + fl;
-      if (f < a.vt_frames) vt[vt_index(dim, f)] = from_f<S>(f < M ? Ct[dim][fl] : 0.f);
-    }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int f = m0 + ty * 4 + i;
-    if (f >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      const int kv = n >= a.d, col = n - kv * a.d, head = col >> 6, dim = col & 63;
-      const float v = acc[i][j] + to_f(bias[n]);
-      out[(((size_t)kv * a.n_head + head) * M + f) * kHeadDim + dim] = from_f<S>(v);
-    }
+  for (int v = 0; v < 16; ++v) {
+    const int f = m0 + wm + 8 * (v >> 2) + 4 * half + (v & 3);
+    if (f < M) out[(((size_t)kv * a.n_head + head) * M + f) * kHeadDim + wn + r32] = acc[v] + bb;
   }
 }
-
 
 // ---------------------------------------------------------------- split-K reduction + LayerNorm
 // h[row] += sum over the partial products (fixed order) + bias; the new h is also
@@ -943,10 +940,16 @@ template <typename S>
 void Ops<S>::hist_write(const HistArgs& a, int n, hipStream_t st) {
   k_hist_write<S><<<dim3(kRows, n, a.nlayer > 0 ? a.nlayer : 1), 256, 0, st>>>(a);
 }
-template <typename S>
-void Ops<S>::gemm_xkv(const XkvArgs& a, hipStream_t st) {
-  const int frames = a.vt_frames > a.n_frames ? a.vt_frames : a.n_frames;  // blocks past n_frames write value padding
-  k_gemm_xkv<S><<<dim3((frames + 63) / 64, 2 * a.d / 64), 256, 0, st>>>(a);
+void gemm_xkv(const XkvArgs& a0, int nslots, hipStream_t st) {
+  const int most = std::max(1, 65535 / a0.nlayer);  // slots per launch (grid z)
+  for (int s = 0; s < nslots; s += most) {
+    XkvArgs a = a0;
+    a.mem += s * a.smem;
+    a.out += s * a.sout_slot;
+    const dim3 grid((a.n_frames + 63) / 64, 2 * a.d / 64, a.nlayer * std::min(most, nslots - s));
+    if (reinterpret_cast<uintptr_t>(a.mem) & 15) k_gemm_xkv<false><<<grid, 256, 0, st>>>(a);
+    else k_gemm_xkv<true><<<grid, 256, 0, st>>>(a);
+  }
 }
 
 void argmax_final(const float* hv, const int* hi, int nblk, int row0, int rows, int* g, float* gmax,
@@ -968,8 +971,7 @@ void accept_greedy(const AcceptArgs& a, hipStream_t st) { k_accept_greedy<<<(a.n
   template void Ops<S>::verify_begin(const BeginArgs&, int, hipStream_t);   \
   template void Ops<S>::draft_begin(const BeginArgs&, int, hipStream_t);    \
   template void Ops<S>::prefill_begin(const BeginArgs&, int, hipStream_t);  \
-  template void Ops<S>::hist_write(const HistArgs&, int, hipStream_t);      \
-  template void Ops<S>::gemm_xkv(const XkvArgs&, hipStream_t);
+  template void Ops<S>::hist_write(const HistArgs&, int, hipStream_t);
 WF_MISC_INST(float)
 WF_MISC_INST(bf16)
 

@@ -892,23 +892,26 @@ struct Runner {
       }
       return;
     }
-    for (int s = 0; s < n; ++s) {
-      const int slot = slot0 + s;
-      const int nblk = c.n_layer + ((c.draft_flags & WF_DRAFT_NO_AUDIO) ? 0 : c.n_draft_layer);
-      for (int l = 0; l < nblk; ++l) {
-        const BlockW& b = l < c.n_layer ? L.tb[l] : L.db[l - c.n_layer];
-        XkvArgs a{};
-        a.mem = reinterpret_cast<const S*>(mem) + s * per;
-        a.w = W(b.w_kv2);
-        a.bias = W(b.b_kv2);
-        a.out = xkv_layer(l) + (size_t)slot * xkv_slot();
-        a.d = c.d_model;
-        a.n_head = c.n_head;
-        a.n_frames = c.n_frames;
-        a.vt_frames = vt_frames();
-        Ops<S>::gemm_xkv(a, st);
-      }
-    }
+    // fp32: one launch for the target blocks of all slots, one for the drafter's
+    auto group = [&](int first, int count, const std::vector<BlockW>& bw) {
+      XkvArgs a{};
+      a.mem = reinterpret_cast<const float*>(mem);
+      a.smem = (long long)per;
+      a.w = reinterpret_cast<const float*>(W(bw[0].w_kv2));
+      a.bias = reinterpret_cast<const float*>(W(bw[0].b_kv2));
+      a.sw = count > 1 ? (long long)(bw[1].w_kv2 - bw[0].w_kv2) : 0;
+      a.sbias = count > 1 ? (long long)(bw[1].b_kv2 - bw[0].b_kv2) : 0;
+      a.out = reinterpret_cast<float*>(xkv_layer(first) + (size_t)slot0 * xkv_slot());
+      a.sout_layer = (long long)c.max_batch * xkv_slot();
+      a.sout_slot = (long long)xkv_slot();
+      a.d = c.d_model;
+      a.n_head = c.n_head;
+      a.n_frames = c.n_frames;
+      a.nlayer = count;
+      gemm_xkv(a, n, st);
+    };
+    group(0, c.n_layer, L.tb);
+    if (!(c.draft_flags & WF_DRAFT_NO_AUDIO)) group(c.n_layer, c.n_draft_layer, L.db);
   }
 
   // The prompt's rows all at once (k_pre.hip).  info: the call's parts and groups in

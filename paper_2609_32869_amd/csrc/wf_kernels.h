@@ -282,14 +282,15 @@ struct AcceptArgs {
   int slot0, n, block_k, eos, n_ctx;
 };
 
-struct XkvArgs {
-  const void* mem;  // [n_frames][d] of one slot
-  const void* w;    // [2d][d]
-  const void* bias; // [2d]
-  void* out;        // block base + slot offset
-  int d, n_head, n_frames;
-  int vt_frames;    // > 0: values stored transposed [head][dim][vt_frames], padding zero
+struct XkvArgs {  // fp32; element strides per layer and per slot
+  const float* mem;   // [n_frames][d] per slot
+  const float* w;     // [2d][d] per layer
+  const float* bias;  // [2d] per layer
+  float* out;         // [2][n_head][n_frames][64] per layer and slot
+  long long smem, sw, sbias, sout_layer, sout_slot;
+  int d, n_head, n_frames, nlayer;
 };
+void gemm_xkv(const XkvArgs& a, int nslots, hipStream_t st);
 
 // Request-time matrix-core GEMM (k_mm.hip): C = A B^T (+ bias) for bf16 A [M, K] and
 // B [N, K] (row-major, k contiguous), fp32 accumulation, 128 x 128 tiles, k in steps
@@ -456,7 +457,6 @@ struct Ops {
   static void draft_begin(const BeginArgs& a, int n, hipStream_t st);
   static void prefill_begin(const BeginArgs& a, int n, hipStream_t st);
   static void hist_write(const HistArgs& a, int n, hipStream_t st);
-  static void gemm_xkv(const XkvArgs& a, hipStream_t st);
 };
 
 template <typename S>

@@ -9,7 +9,8 @@ import numpy as np
 import pytest
 import torch
 
-from wf_fixtures import MICRO, MICRO_ENC, make_encoder_weights, make_audio, make_weights, make_prefix
+from wf_fixtures import (MICRO, MICRO_ENC, make_encoder_weights, make_audio, make_memory, make_weights,
+                         make_prefix)
 from oracle import OracleOpts
 from oracle.encoder import Encoder
 from oracle.numerics import bf16
@@ -96,3 +97,23 @@ def test_frontend_window_lengths(n_fft):
     enc.close()
     want = log_mel(x, ecfg.n_mels, n_fft)
     np.testing.assert_allclose(got, want[:, :got.shape[1]], rtol=0, atol=1e-5)
+
+
+@pytest.mark.parametrize("n_frames,offset", [(65, 0), (64, 1)])
+def test_fp32_acoustic_keys_and_values(n_frames, offset):
+    """fp32 storage: the keys and values of every block and slot in one launch, a last tile of
+    one frame, and an acoustic memory that is not 16-byte aligned."""
+    from lockstep import Lockstep
+    cfg = MICRO.with_(name="xkv-f32", n_frames=n_frames)
+    W = make_weights(cfg)
+    ls = Lockstep(cfg, W, [make_prefix(cfg, i, 7 + i) for i in range(3)], [20] * 3, 1e-3,
+                  opts=OracleOpts(dtype=np.float32))
+    if offset:  # the same memory again from an address 4 bytes past a multiple of 16
+        mem = torch.from_numpy(np.stack([make_memory(cfg, i) for i in range(3)]).astype(np.float32))
+        shifted = torch.empty(mem.numel() + 4, device="cuda")[offset:offset + mem.numel()].view(mem.shape)
+        shifted.copy_(mem)
+        ls.eng.encode_memory_set(0, shifted)
+    for _ in range(3):
+        ls.step()
+    assert ls.steps == 3
+    ls.close()
