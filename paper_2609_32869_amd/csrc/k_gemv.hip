@@ -1134,8 +1134,10 @@ __global__ void __launch_bounds__(NW * 64) k_gemv_f32(GemvArgs a) {
   const int nb = blockIdx.x * 16;
   const int K = a.K, lda = a.a.ld;
   const int KS = K / 16;
-  const int spw = (KS + NW - 1) / NW;
-  const int s0 = min(KS, wv * spw), s1 = min(KS, s0 + spw);
+  // grid y splits the k-steps (EPI_PART; a split past the end stores zeros), the waves a split's
+  const int kss = (KS + gridDim.y - 1) / gridDim.y, spw = (kss + NW - 1) / NW;
+  const int kb = min(KS, (int)blockIdx.y * kss), ke = min(KS, kb + kss);
+  const int s0 = min(ke, kb + wv * spw), s1 = min(ke, s0 + spw);
   const float* wp = W + (size_t)min(nb + col, a.N - 1) * K + kg * 4;
   for (int tile0 = a.mt0; tile0 < a.mt1; tile0 += 2) {
     const bool two = tile0 + 1 < a.mt1;
@@ -1251,7 +1253,7 @@ static void launch_bf16(const GemvArgs& a, hipStream_t st) {
 }
 template <int EPI, int NW>
 static void launch_f32(const GemvArgs& a, hipStream_t st) {
-  k_gemv_f32<EPI, NW><<<(a.N + 15) / 16, NW * 64, 0, st>>>(a);
+  k_gemv_f32<EPI, NW><<<dim3((a.N + 15) / 16, EPI == EPI_PART && a.ksplit > 1 ? a.ksplit : 1), NW * 64, 0, st>>>(a);
 }
 
 // 16 waves: one row of the LayerNorm per wave; K <= kLnFoldMaxK gives at most
@@ -1331,7 +1333,8 @@ static void launch_epi(const GemvArgs& a, hipStream_t st) {
   }
   // waves per block: enough that each wave's share of the k-steps fits one batch
   const int kstep = sizeof(S) == 4 ? 16 : (a.wkind == W_F32 ? 16 : 32);
-  const int steps = a.K / kstep;
+  const int ksp = EPI == EPI_PART && sizeof(S) == 4 && a.ksplit > 1 ? a.ksplit : 1;
+  const int steps = (a.K / kstep + ksp - 1) / ksp;
   if constexpr (sizeof(S) == 4) {
     if (steps <= 4 * kU) launch_f32<EPI, 4>(a, st);
     else if (steps <= 8 * kU || EPI == EPI_ARGMAX) launch_f32<EPI, 8>(a, st);  // the head's epilogue needs > 128 VGPRs

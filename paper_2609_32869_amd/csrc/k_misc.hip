@@ -845,7 +845,6 @@ __global__ void __launch_bounds__(kRlnThreads) k_reduce_ln(RlnArgs a) {
 // consecutive columns, loaded and written 16 bytes at a time (h, the tap and the
 // operand), statistics as wave sums merged in LDS.  The sums are formed in the
 // order of k_reduce_ln: h + ((p0 + p1 + ...) + bias).
-constexpr int kRlnRowParts = 4;
 constexpr int kRlnColThreads = 192;
 template <typename S>
 __global__ void __launch_bounds__(kRlnColThreads) k_reduce_ln_rows(RlnArgs a) {

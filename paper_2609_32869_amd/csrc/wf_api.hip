@@ -264,6 +264,18 @@ int compute_layout(const wf_config& c, Layout& L) {
   L.part = region((size_t)nparts * R9 * d * 4);
   const size_t xrec = c.dtype == WF_BF16 ? B * H * (size_t)cross_mx_chunks(1, c.n_frames) : 0;  // 1 slot: the smallest chunks
   L.xpart = region(std::max((size_t)kXrMaxPartials, xrec) * kXrPart * 4);
+  // fp32 storage: blocks of 16 columns, each taking all rows, split over k likewise (at most
+  // kRlnRowParts buffers, which the row-per-block reduction takes): 384 columns are 24
+  // blocks, 17 us for K = 1536, 6.9 split four ways, and the reduction's launch
+  // replaces the next LayerNorm's.  The partial sums use the cross-attention's records,
+  // which are free then.
+  L.fc2_part = L.part;
+  if (c.dtype == WF_F32) {
+    const int tiles16 = (int)((d + 15) / 16), fit = (int)((size_t)kXrMaxPartials * kXrPart / (R9 * d));
+    const int ks = std::min({kRlnRowParts, fit, 240 / tiles16, (int)(F / 16)});
+    L.fc2_split = ks > 1 ? ks : 0;
+    if (L.fc2_split) L.fc2_part = L.xpart;
+  }
   L.lncd = region(L.nsplit_op == 3 ? cw * 4 : 0);
   L.stamps = region((size_t)kStampSlots * kStampWords * 8);
   // prompt pass over many rows: every prompt of a call up to kPreMaxRows rows, the
@@ -641,14 +653,14 @@ struct Runner {
       tap_next = tap;
     } else if (ksplit > 0) {
       // k-split partial sums, then h += sum + bias, the tap, and the next LayerNorm
-      GemvArgs a = gemv_args(slot0, n, Af16(), b.w_fc2, b.b_fc2, c.d_ff, d, F32(L.part), d, Operand{nullptr, 0, OP_ROW, 0}, -1);
+      GemvArgs a = gemv_args(slot0, n, Af16(), b.w_fc2, b.b_fc2, c.d_ff, d, F32(L.fc2_part), d, Operand{nullptr, 0, OP_ROW, 0}, -1);
       a.bias = nullptr;
       a.ct = 4;
       a.ksplit = ksplit;
       a.pstride = (size_t)R9() * d;
       run_gemv("gemv_fc2", EPI_PART, n, a);
       RlnArgs ra{};
-      ra.part = F32(L.part); ra.nparts = ksplit; ra.pstride = (size_t)R9() * d; ra.bias = W(b.b_fc2); ra.h = h_;
+      ra.part = F32(L.fc2_part); ra.nparts = ksplit; ra.pstride = (size_t)R9() * d; ra.bias = W(b.b_fc2); ra.h = h_;
       ra.tap = Atap16(); ra.tapcol = tap >= 0 ? tap * d : -1; ra.g = W(nx.g); ra.b = W(nx.b); ra.out = nx.wide ? Ad32() : Ad16();
       ra.d = d; ra.row0 = slot0 * kRows; ra.nsplit = L.nsplit_op; ra.R9 = R9();
       launch("reduce_ln", 4.0 * kRows * n * d * (ksplit + 3), [&](unsigned long long* sp) {

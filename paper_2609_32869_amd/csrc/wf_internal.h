@@ -50,6 +50,7 @@ struct Layout {
   int mt16, mt32; // 16-row / 32-row tiles held by an operand buffer
   size_t stage_bytes;  // raw-matrix staging at init (inside the cross K/V region)
   int fc2_split;       // k-splits of the second MLP product (0: not split)
+  size_t fc2_part;     // its partial sums
 };
 
 struct Handle;

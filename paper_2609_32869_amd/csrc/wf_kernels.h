@@ -468,6 +468,7 @@ void repack(const void* src, void* dst, int N, int K, int wkind, hipStream_t st)
 void ln_fold_cols(const void* w, const void* g, const void* b, int N, int K, float* c, float* e, hipStream_t st);
 
 constexpr int kRlnMaxPartsHost = 16;
+constexpr int kRlnRowParts = 4;  // partial buffers that the row-per-block reduction takes
 constexpr int kSampleBlocks = 64;     // vocabulary slices of a sampling draw per slot  // most split-K partials a reduction sums
 
 // largest row length K of a product with the LayerNorm folded in (its operand is

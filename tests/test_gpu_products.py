@@ -117,3 +117,18 @@ def test_fp32_acoustic_keys_and_values(n_frames, offset):
         ls.step()
     assert ls.steps == 3
     ls.close()
+
+
+@pytest.mark.parametrize("d_ff", [32, 96, 352])
+def test_fp32_second_mlp_product_split(d_ff):
+    """fp32 storage: k-splits of one step (two splits), an empty last split, and splits that
+    do not divide the k-steps."""
+    from lockstep import Lockstep
+    cfg = MICRO.with_(name="fc2-f32", d_ff=d_ff)
+    W = make_weights(cfg)
+    ls = Lockstep(cfg, W, [make_prefix(cfg, i, 7 + i) for i in range(2)], [20] * 2, 1e-3,
+                  opts=OracleOpts(dtype=np.float32))
+    for _ in range(3):
+        ls.step()
+    assert ls.steps == 3
+    ls.close()
