@@ -272,6 +272,27 @@ __device__ __forceinline__ float rng_uniform(uint64_t x) { return ((float)(x >> 
 // Gumbel noise -log(-log(u)) in fp32
 __device__ __forceinline__ float rng_gumbel(uint64_t x) { return -logf(-logf(rng_uniform(x))); }
 
-__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752440f)); }
+// x Phi(x) = max(x, 0) - |x| Q(|x|), Q the normal distribution's upper tail as
+// exp(-z^2 / 2) t P(t), t = 1 / (1 + 0.34 z): P of degree 8 fitted to erfcx by weighted least
+// squares on 0 <= z <= 14 (relative error 3e-8).  About half the instructions of
+// 0.5 x (1 + erf(x / sqrt(2))) through erff, whose two ranges both run where a wave's lanes
+// differ (8.5 of 31 us per tile of the encoder's first MLP product): four requests through
+// the encoder 13.68 -> 12.93 ms, one 5.14 -> 4.90.
+// On -8 .. 8 in fp32, against 64 bits: largest error 2.4e-7 (4.5e-7 with erff), rms 5.1e-8
+// (6.8e-8), and no cancellation for negative x.
+__device__ __forceinline__ float gelu_erf(float x) {
+  const float z = fabsf(x), t = __builtin_amdgcn_rcpf(fmaf(0.34f, z, 1.0f));
+  float p = -0.0261201616f;
+  p = fmaf(p, t, 0.1394981f);
+  p = fmaf(p, t, -0.273130119f);
+  p = fmaf(p, t, 0.202179939f);
+  p = fmaf(p, t, -0.0447167344f);
+  p = fmaf(p, t, 0.115358502f);
+  p = fmaf(p, t, 0.115197815f);
+  p = fmaf(p, t, 0.136112183f);
+  p = fmaf(p, t, 0.135620505f);
+  const float s = z * 0.849321800288019f;  // z^2 log2(e) / 2 = s^2
+  return fmaf(-z, p * t * __builtin_amdgcn_exp2f(-s * s), fmaxf(x, 0.0f));
+}
 
 }  // namespace wf
