@@ -279,7 +279,8 @@ __device__ __forceinline__ float rng_gumbel(uint64_t x) { return -logf(-logf(rng
 // differ (8.5 of 31 us per tile of the encoder's first MLP product): four requests through
 // the encoder 13.68 -> 12.93 ms, one 5.14 -> 4.90.
 // On -8 .. 8 in fp32, against 64 bits: largest error 2.4e-7 (4.5e-7 with erff), rms 5.1e-8
-// (6.8e-8), and no cancellation for negative x.
+// (6.8e-8), and no cancellation for negative x.  The factor |x| stays finite for x = +inf,
+// where Q is zero: +inf, as with erff; -inf and NaN give NaN, as there.
 __device__ __forceinline__ float gelu_erf(float x) {
   const float z = fabsf(x), t = __builtin_amdgcn_rcpf(fmaf(0.34f, z, 1.0f));
   float p = -0.0261201616f;
@@ -292,7 +293,7 @@ __device__ __forceinline__ float gelu_erf(float x) {
   p = fmaf(p, t, 0.136112183f);
   p = fmaf(p, t, 0.135620505f);
   const float s = z * 0.849321800288019f;  // z^2 log2(e) / 2 = s^2
-  return fmaf(-z, p * t * __builtin_amdgcn_exp2f(-s * s), fmaxf(x, 0.0f));
+  return fmaf(-fabsf(fminf(x, __FLT_MAX__)), p * t * __builtin_amdgcn_exp2f(-s * s), fmaxf(x, 0.0f));
 }
 
 }  // namespace wf

@@ -6,10 +6,13 @@ rounding (u = 2^-24) at a condition of at most 2.4 (sum |c_i| over P(1)), 19 u; 
 roundings at a sensitivity below 4, 8 u; three products, 3 u; s^2 = z^2 log2(e) / 2 with
 three roundings in the exponent, 1.5 z^2 u.  The last sum rounds to u of the result.
 """
+import ctypes
 import pathlib
 import re
+import subprocess
 
 import numpy as np
+import pytest
 
 SRC = pathlib.Path(__file__).parents[1] / "paper_2609_32869_amd" / "csrc" / "wf_common.h"
 
@@ -43,3 +46,36 @@ def test_gelu_formula():
     bound = tail * (3.1e-8 + (30 + 1.5 * z.astype(np.float64) ** 2) * eps) + eps * np.abs(want) + 1e-30
     err = np.abs(got - want)
     assert (err <= bound).all() and err.max() <= 2.5e-7
+
+
+@pytest.fixture(scope="module")
+def gelu(tmp_path_factory):
+    """The header's function, compiled for the host with exact division and exp2."""
+    text = SRC.read_text()
+    at = text.index("float gelu_erf(float x)")
+    function = text[at:text.index("\n}", at) + 2]
+    folder = tmp_path_factory.mktemp("gelu")
+    (folder / "gelu.cpp").write_text(
+        "#include <cmath>\nusing namespace std;\n"
+        "static float __builtin_amdgcn_rcpf(float x) { return 1.0f / x; }\n"
+        "static float __builtin_amdgcn_exp2f(float x) { return (float)exp2((double)x); }\n"
+        f"static {function}\n"
+        'extern "C" void run(const float* x, float* y, long n) { for (long i = 0; i < n; ++i) y[i] = gelu_erf(x[i]); }\n')
+    # every fma and rounding as written
+    subprocess.run(["g++", "-O1", "-ffp-contract=off", "-shared", "-fPIC", "-o", folder / "gelu.so", folder / "gelu.cpp"],
+                   check=True)
+    lib = ctypes.CDLL(str(folder / "gelu.so"))
+
+    def run(x):
+        x = np.ascontiguousarray(x, np.float32)
+        y = np.empty_like(x)
+        lib.run(ctypes.c_void_p(x.ctypes.data), ctypes.c_void_p(y.ctypes.data), ctypes.c_long(x.size))
+        return y
+    return run
+
+
+def test_gelu_limits(gelu):
+    inf, big = np.float32(np.inf), np.finfo(np.float32).max
+    y = gelu(np.array([inf, big, 1e30, -big, -1e30, -40, 0], np.float32))
+    assert y.tolist() == [inf, big, np.float32(1e30), 0, 0, 0, 0]
+    assert np.isnan(gelu(np.array([-inf, np.nan], np.float32))).all()
