@@ -1,10 +1,11 @@
-"""The kernels' GELU formula (coefficients read from its source), evaluated in fp32 on the
-host, against 64 bits.
+"""The kernels' GELU (its function compiled for the host from the kernels' header, with exact
+division and exp2 in place of the two instructions) against 64 bits.
 
-Bound, relative to the tail |x| Q(|x|): the fit's error (3e-8); eight Horner steps of one
-rounding (u = 2^-24) at a condition of at most 2.4 (sum |c_i| over P(1)), 19 u; t with two
-roundings at a sensitivity below 4, 8 u; three products, 3 u; s^2 = z^2 log2(e) / 2 with
-three roundings in the exponent, 1.5 z^2 u.  The last sum rounds to u of the result.
+Bound: Q = E (1 / 2 + s G(s)) with q = erfcx(z / sqrt(2)) / 2 its second factor.  The fit is
+within 1e-8 of q, the stored coefficients within u (u = 2^-24) of theirs, and ten fused steps
+round once each: 11 u (1 / 2 + sum |c_i| s^(i + 1)); s has three roundings, the reciprocal one
+more, each to within 2 u: 5 u sum (i + 1) |c_i| s^(i + 1).  E has 1 u, and y^2 in its
+exponent three roundings: 1.5 z^2 u; their product 1 u.  The last sum rounds to u of the result.
 """
 import ctypes
 import pathlib
@@ -13,47 +14,21 @@ import subprocess
 
 import numpy as np
 import pytest
+from scipy.special import erfc, erfcx
 
 SRC = pathlib.Path(__file__).parents[1] / "paper_2609_32869_amd" / "csrc" / "wf_common.h"
-
-
-def test_gelu_formula():
-    from scipy.special import erfc
-    body = re.search(r"float gelu_erf\(float x\) \{(.*?)\n\}", SRC.read_text(), re.S).group(1)
-    c = float(re.search(r"fmaf\(([\d.]+)f, z, 1\.0f\)", body).group(1))
-    poly = [float(re.search(r"float p = (\S+?)f;", body).group(1))]
-    poly += [float(v) for v in re.findall(r"p = fmaf\(p, t, (\S+?)f\);", body)]
-    scale = float(re.search(r"s = z \* ([\d.]+)f;", body).group(1))
-    assert len(poly) == 9
-    f = np.float32
-
-    def fma(a, b, d):
-        return (a.astype(np.float64) * np.float64(b) + np.float64(d)).astype(f)
-
-    x = np.linspace(-8, 8, 100001).astype(f)
-    z = np.abs(x)
-    t = (f(1) / fma(z, f(c), 1.0)).astype(f)
-    p = np.full_like(z, poly[0])
-    for k in poly[1:]:
-        p = fma(p, t, f(k))
-    s = z * f(scale)
-    q = (p * t) * np.exp2((-s * s).astype(np.float64)).astype(f)
-    got = (np.maximum(x, f(0)).astype(np.float64) - z.astype(np.float64) * q).astype(f)
-    x64 = x.astype(np.float64)
-    want = 0.5 * x64 * erfc(-x64 / np.sqrt(2))
-    eps = 2.0 ** -24
-    tail = z * 0.5 * erfc(z.astype(np.float64) / np.sqrt(2))
-    bound = tail * (3.1e-8 + (30 + 1.5 * z.astype(np.float64) ** 2) * eps) + eps * np.abs(want) + 1e-30
-    err = np.abs(got - want)
-    assert (err <= bound).all() and err.max() <= 2.5e-7
+U = 2.0 ** -24
 
 
 @pytest.fixture(scope="module")
-def gelu(tmp_path_factory):
-    """The header's function, compiled for the host with exact division and exp2."""
+def function():
     text = SRC.read_text()
     at = text.index("float gelu_erf(float x)")
-    function = text[at:text.index("\n}", at) + 2]
+    return text[at:text.index("\n}", at) + 2]
+
+
+@pytest.fixture(scope="module")
+def gelu(function, tmp_path_factory):
     folder = tmp_path_factory.mktemp("gelu")
     (folder / "gelu.cpp").write_text(
         "#include <cmath>\nusing namespace std;\n"
@@ -72,6 +47,37 @@ def gelu(tmp_path_factory):
         lib.run(ctypes.c_void_p(x.ctypes.data), ctypes.c_void_p(y.ctypes.data), ctypes.c_long(x.size))
         return y
     return run
+
+
+def exact(x):
+    x = x.astype(np.float64)
+    return 0.5 * x * erfc(-x / np.sqrt(2))
+
+
+def test_gelu_formula(gelu, function):
+    c = float(re.search(r"([\d.]+)f \* z", function).group(1))
+    g = [float(v) for v in re.findall(r"g, s, (-?[\d.e-]+)f\);", function)]
+    g = [float(re.search(r"float g = (\S+?)f;", function).group(1))] + g
+    assert len(g) == 9
+    x = np.linspace(-8, 8, 100001).astype(np.float32)
+    z = np.abs(x).astype(np.float64)
+    s = c * z / (1 + c * z)
+    size = [abs(k) * s ** (9 - i) for i, k in enumerate(g)]  # |c_i| s^(i + 1), highest first
+    slope = [(9 - i) * v for i, v in enumerate(size)]
+    q, E = erfcx(z / np.sqrt(2)) / 2, np.exp(-z * z / 2)
+    bound = z * E * (1e-8 * q + U * (11 * (0.5 + sum(size)) + 5 * sum(slope)) + U * q * (2 + 1.5 * z * z))
+    want = exact(x)
+    err = np.abs(gelu(x) - want)
+    assert (err <= bound + U * np.abs(want) + 1e-30).all() and err.max() <= 2.5e-7
+
+
+def test_gelu_keeps_small_values(gelu):
+    """Relative error near zero, where 0.5 x (1 + erf(x / sqrt(2))) in fp32 is within 2 u."""
+    x = np.linspace(-0.2, 0.2, 100001).astype(np.float32)
+    x = x[x != 0]
+    want = exact(x)
+    err = np.abs(gelu(x) - want) / np.abs(want)
+    assert err.max() <= 2.7 * U and np.sqrt((err ** 2).mean()) <= 0.7 * U
 
 
 def test_gelu_limits(gelu):
