@@ -68,6 +68,7 @@ __global__ void __launch_bounds__(256) k_pre_last(PreArgs a, float* __restrict__
 // and 16 bytes wide.
 template <int P>
 __global__ void __launch_bounds__(256) k_pre_rln(PreLnArgs a) {
+  StampScope stamp_scope(a.stamp, blockDim.x);
   __shared__ float red[2][4];
   const int row = blockIdx.x, d = a.d, nch = d >> 3, c = threadIdx.x, cc = min(c, nch - 1);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
@@ -137,6 +138,7 @@ __global__ void __launch_bounds__(256) k_pre_rln(PreLnArgs a) {
 // (PRE_PART: one buffer of partial sums per split).
 template <int EPI, int P, int WK, int TI, int TJ, int D>
 __global__ void __launch_bounds__(256, 1) k_pre_gemm(PreGemmArgs a, int nmb, int nnb, int rs) {
+  StampScope stamp_scope(a.stamp, 256);
   constexpr int NW = 4, Q = TI * TJ / NW;
   __shared__ float4 red[NW - 1][Q < 2 ? 1 : 2][4][NW][64];
   int mbk, nbk;
@@ -240,6 +242,7 @@ __device__ __forceinline__ float quad_rows(float v, bool max) {  // over the fou
 
 template <bool CROSS, int P, int NQ, int NW, int ND>
 __global__ void __launch_bounds__(NW * 64, NW / 4) k_pre_attn(PreAttnArgs a) {
+  StampScope stamp_scope(a.stamp, NW * 64);
   constexpr int kOld = 68;  // padded row of the wave outputs
   __shared__ float wmax[NQ][NW][16], wsum[NQ][NW][16];
   __shared__ float wo[NQ][NW][16][kOld];

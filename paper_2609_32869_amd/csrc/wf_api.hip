@@ -942,19 +942,28 @@ struct Runner {
     auto Wb = [&](size_t off) { return reinterpret_cast<const bf16*>(W(off)); };
     for (const PrePass& ps : plan.passes) {
       const int rows = ps.nparts * kPrePart;
+      int nslots = 0;
+      for (int i = 0; i < ps.nparts; ++i)
+        nslots += i == 0 || plan.parts[ps.part0 + i].slot != plan.parts[ps.part0 + i - 1].slot;
       PreArgs pa{};
       pa.parts = parts + ps.part0; pa.tokens = tokens; pa.emb = W(L.tok_emb); pa.emb_kind = wk(true); pa.pos = W(L.pos_emb);
       pa.h = h_; pa.slot0 = slot0; pa.pmax = pmax; pa.d = d; pa.n_vocab = c.n_vocab;
       pre_begin(pa, ps.nparts, st);
-      // y = A W^T in the given epilogue; returns the k-splits of PRE_PART
-      auto product = [&](int epi, const bf16* a, size_t w, size_t b, int N, int K, float* y, int ldy, bf16* aout,
+      // y = A W^T in the given epilogue; returns the k-splits of PRE_PART.  The launches'
+      // classes in a profile are the step's
+      auto product = [&](const char* tag, int epi, const bf16* a, size_t w, size_t b, int N, int K, float* y, int ldy, bf16* aout,
                          S* cache = nullptr, bool wide = false) {
         PreGemmArgs g{};
         g.a = a; g.mt = mt; g.w = Wb(w); g.wkind = wk(wide); g.bias = Wb(b); g.M = rows; g.N = N; g.K = K;
         g.y = y; g.ldy = ldy; g.pstride = (size_t)L.pre_rows * d; g.aout = aout;
         g.parts = pa.parts; g.page_table = ptab; g.pages_per_slot = L.pages_per_slot; g.d = d; g.n_head = c.n_head;
         g.cache = cache; g.kv_stride = kv_stride();
-        return pre_gemm(epi, g, planes, st);
+        int ks = 1;
+        launch(tag, eb() * N * (K + 1.0) + planes * eb() * rows * K + 4.0 * rows * N, [&](unsigned long long* sp) {
+          g.stamp = sp;
+          ks = pre_gemm(epi, g, planes, st);
+        });
+        return ks;
       };
       // h += partial sums + bias, the tap of a tapped block, and the next LayerNorm
       auto reduce = [&](int nparts, size_t b, size_t lg, size_t lb, bool ln, int tap = -1, bool fresh = false) {
@@ -962,14 +971,20 @@ struct Runner {
         r.h = h_; r.part = part; r.pstride = (size_t)L.pre_rows * d; r.nparts = nparts; r.fresh = fresh ? 1 : 0;
         r.bias = Wb(b); r.tap = Atap; r.tapcol = tap >= 0 ? tap * d : -1; r.tapld = c.n_tap * d;
         r.g = ln ? Wb(lg) : nullptr; r.b = Wb(lb); r.out = A; r.mt = mt; r.d = d;
-        pre_rln(r, planes, rows, st);
+        launch(nparts > 0 ? "reduce_ln" : "layernorm", 4.0 * rows * d * (nparts + 1 + planes * eb() / 4.0), [&](unsigned long long* sp) {
+          r.stamp = sp;
+          pre_rln(r, planes, rows, st);
+        });
       };
       auto attend = [&](bool cross, const S* k, const S* v) {
         PreAttnArgs t{};
         t.q = q; t.ldq = d; t.k = k; t.v = v; t.parts = pa.parts; t.groups = groups + ps.group0; t.page_table = ptab;
         t.pages_per_slot = L.pages_per_slot; t.n_frames = c.n_frames; t.vt_frames = vt_frames(); t.d = d; t.n_head = c.n_head;
         t.out = A; t.mt = mt;
-        pre_attn(t, cross, planes, plan.nq, ps.ngroups, st);
+        launch(cross ? "attn_cross" : "attn_self", cross ? 2.0 * d * c.n_frames * eb() * nslots : 0.0, [&](unsigned long long* sp) {
+          t.stamp = sp;
+          pre_attn(t, cross, planes, plan.nq, ps.ngroups, st);
+        });
       };
       reduce(0, 0, L.tb[0].ln1_g, L.tb[0].ln1_b, true);
       for (int l = 0; l < c.n_layer; ++l) {
@@ -977,16 +992,16 @@ struct Runner {
         int tap = -1;
         for (int i = 0; i < c.n_tap; ++i)
           if (c.taps[i] == l) tap = i;
-        product(PRE_QKV, A, b.w_qkv, b.b_qkv, 3 * d, d, q, d, nullptr, skv_layer(l));
+        product("gemv_qkv", PRE_QKV, A, b.w_qkv, b.b_qkv, 3 * d, d, q, d, nullptr, skv_layer(l));
         attend(false, skv_layer(l), skv_layer(l) + kv_stride());
-        int ks = product(PRE_PART, A, b.w_o, b.b_o, d, d, part, d, nullptr);
+        int ks = product("gemv_o", PRE_PART, A, b.w_o, b.b_o, d, d, part, d, nullptr);
         reduce(ks, b.b_o, b.ln2_g, b.ln2_b, true);
-        product(PRE_STORE, A, b.w_q2, b.b_q2, d, d, q, d, nullptr);
+        product("gemv_q2", PRE_STORE, A, b.w_q2, b.b_q2, d, d, q, d, nullptr);
         attend(true, xkv_layer(l), nullptr);
-        ks = product(PRE_PART, A, b.w_o2, b.b_o2, d, d, part, d, nullptr);
+        ks = product("gemv_o", PRE_PART, A, b.w_o2, b.b_o2, d, d, part, d, nullptr);
         reduce(ks, b.b_o2, b.ln3_g, b.ln3_b, true);
-        product(PRE_GELU, A, b.w_fc1, b.b_fc1, F, d, nullptr, 0, Af, nullptr, true);
-        ks = product(PRE_PART, Af, b.w_fc2, b.b_fc2, d, F, part, d, nullptr);
+        product("gemv_fc1", PRE_GELU, A, b.w_fc1, b.b_fc1, F, d, nullptr, 0, Af, nullptr, true);
+        ks = product("gemv_fc2", PRE_PART, Af, b.w_fc2, b.b_fc2, d, F, part, d, nullptr);
         const bool more = l + 1 < c.n_layer;
         reduce(ks, b.b_fc2, more ? L.tb[l + 1].ln1_g : 0, more ? L.tb[l + 1].ln1_b : 0, more, tap);
       }
@@ -994,11 +1009,11 @@ struct Runner {
       if (c.draft_flags & WF_DRAFT_NO_HISTORY) continue;
       // drafter history: the taps' projection in place of the residual rows, then
       // every block's LayerNorm, k | v product and cache rows
-      const int ks = product(PRE_PART, Atap, L.hproj_w, L.hproj_b, d, c.n_tap * d, part, d, nullptr);
+      const int ks = product("gemv_hproj", PRE_PART, Atap, L.hproj_w, L.hproj_b, d, c.n_tap * d, part, d, nullptr);
       for (int dl = 0; dl < c.n_draft_layer; ++dl) {
         const BlockW& b = L.db[dl];
         reduce(dl == 0 ? ks : 0, L.hproj_b, b.ln1_g, b.ln1_b, true, -1, true);
-        product(PRE_STORE, A, b.w_qkv + (size_t)d * d, b.b_qkv + d, 2 * d, d, part, 2 * d, nullptr);
+        product("gemv_hist_kv", PRE_STORE, A, b.w_qkv + (size_t)d * d, b.b_qkv + d, 2 * d, d, part, 2 * d, nullptr);
         PreHistArgs ha{};
         ha.kv = part; ha.parts = pa.parts; ha.kcache = hkv(dl, 0); ha.vcache = hkv(dl, 1); ha.rope = F32(L.rope);
         ha.use_rope = !(c.draft_flags & WF_DRAFT_ABS_POS); ha.d = d; ha.n_head = c.n_head; ha.n_ctx = c.n_ctx;

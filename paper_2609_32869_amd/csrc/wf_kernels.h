@@ -399,6 +399,7 @@ struct PreLnArgs {
   const bf16* b;
   bf16* out;
   int mt, d;          // 16-row tiles held by the operand buffers
+  unsigned long long* stamp;  // launch timing slot (profiled calls), or null
 };
 enum { PRE_STORE = 0, PRE_PART = 1, PRE_GELU = 2, PRE_QKV = 3 };
 struct PreGemmArgs {
@@ -417,6 +418,7 @@ struct PreGemmArgs {
   int pages_per_slot, d, n_head;
   void* cache;
   size_t kv_stride;
+  unsigned long long* stamp;
 };
 struct PreAttnArgs {
   const float* q;
@@ -429,6 +431,7 @@ struct PreAttnArgs {
   int pages_per_slot, n_frames, vt_frames, d, n_head;
   bf16* out;
   int mt;
+  unsigned long long* stamp;
 };
 struct PreHistArgs {
   const float* kv;    // [rows][2d]

@@ -92,3 +92,26 @@ def test_refill_leaves_other_slots():
     for _ in range(2):
         ls.step()
     ls.close()
+
+
+@pytest.mark.parametrize("lens", [[9], [40], [40, 23]])
+def test_profile_names_the_prompt_pass(lens):
+    """A profiled prompt call times every product, attention and LayerNorm launch, in the
+    nine-row passes (9 tokens) as in the many-row one."""
+    cfg = MICRO.with_(name="micro-bf16-pre", dtype="bf16", n_vocab=501)
+    ls = _run(cfg, lens, TOL_MICRO, steps=0)
+    prompt = np.stack([np.resize(make_prefix(cfg, i, n), max(lens)) for i, n in enumerate(lens)])
+    ls.eng.profile(True)
+    ls.eng.prefill(0, torch.from_numpy(prompt).cuda(), lens, [cfg.n_ctx] * len(lens))
+    prof = ls.eng.profile_summary()
+    ls.eng.profile(False)
+    ls.close()
+    L, D = cfg.n_layer, cfg.n_draft_layer
+    want = {"gemv_qkv": L, "attn_self": L, "gemv_q2": L, "attn_cross": L, "gemv_fc1": L, "gemv_fc2": L, "gemv_hproj": 1,
+            "gemv_hist_kv": D, "head": 1}
+    if lens != [9]:
+        want |= {"gemv_o": 2 * L, "reduce_ln": 3 * L + 1, "layernorm": 1 + D - 1}
+    for role, n in want.items():
+        assert prof.get(role, {}).get("launches", 0) >= n and prof[role]["exec_ms"] > 0, (role, prof.get(role))
+        if lens != [9] and role not in ("layernorm", "attn_cross"):
+            assert prof[role]["launches"] == n, (role, prof[role])
