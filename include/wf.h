@@ -95,7 +95,9 @@ typedef struct wf_config {
 
 typedef struct wf_handle wf_handle;
 
-/* Number of workspace bytes a handle with this config needs. */
+/* Number of workspace bytes of a handle with this config.  With bf16 storage they hold
+ * the buffers of the many-row prompt pass (large-v3: 48 MB with one slot, 168 MB with
+ * five or more), which wf_init_weights can do without. */
 int wf_workspace_bytes(const wf_config* cfg, size_t* bytes);
 
 /* Number of parameter tensors wf_init_weights expects, and the element count
@@ -105,7 +107,9 @@ int wf_weight_numel(const wf_config* cfg, int i, int64_t* numel);
 
 /*
  * Create a handle over `workspace` (device, ws_bytes >= wf_workspace_bytes,
- * 256-byte aligned) and copy the parameters into it.
+ * 256-byte aligned) and copy the parameters into it.  bf16 storage also takes a
+ * workspace that lacks only the many-row prompt pass's buffers: every prompt then runs
+ * nine positions per pass.
  *
  * weights: host array of n_weights device pointers, one per parameter in the
  * manifest order, each holding its tensor in the storage type, row-major,

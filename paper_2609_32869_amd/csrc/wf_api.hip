@@ -163,7 +163,7 @@ std::vector<ManEntry> manifest(const wf_config& c, const Layout& L, std::vector<
 
 namespace wf {
 
-int compute_layout(const wf_config& c, Layout& L) {
+int compute_layout(const wf_config& c, Layout& L, bool many_rows) {
   const size_t d = c.d_model, F = c.d_ff, V = c.n_vocab, B = c.max_batch, H = c.n_head;
   const size_t R9 = B * kRows;
   const size_t eb = elt_bytes(c);
@@ -280,7 +280,7 @@ int compute_layout(const wf_config& c, Layout& L) {
   L.stamps = region((size_t)kStampSlots * kStampWords * 8);
   // prompt pass over many rows: every prompt of a call up to kPreMaxRows rows, the
   // operands as bf16 planes
-  L.pre_rows = c.dtype == WF_BF16 ? (int)std::min(B * (size_t)c.n_ctx, (size_t)kPreMaxRows) : 0;
+  L.pre_rows = many_rows && c.dtype == WF_BF16 ? (int)std::min(B * (size_t)c.n_ctx, (size_t)kPreMaxRows) : 0;
   const size_t PR = L.pre_rows, pb = (size_t)L.nsplit_op * 2;
   L.pre_h = region(PR * d * 4);
   L.pre_q = region(PR * d * 4);
@@ -1182,6 +1182,8 @@ int wf_init_weights(wf_handle** out, const wf_config* cfg, const void* const* we
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255)) return fail(nullptr, WF_EINVAL, "workspace must be 256-byte aligned");
   Layout L;
   compute_layout(*cfg, L);
+  // without room for the many-row prompt pass: nine positions per pass
+  if (ws_bytes < L.total) compute_layout(*cfg, L, false);
   if (ws_bytes < L.total) return fail(nullptr, WF_ESIZE, "workspace too small");
   auto man = manifest(*cfg, L);
   if (!weights || n_weights != (int)man.size()) return fail(nullptr, WF_EINVAL, "wrong number of weight tensors");

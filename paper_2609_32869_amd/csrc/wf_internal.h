@@ -36,7 +36,7 @@ struct Layout {
   // prompt pass over many rows (bf16): residual rows, queries, operands, partial
   // sums and the call's parts
   size_t pre_h, pre_q, pre_a, pre_f, pre_tap, pre_part, pre_info;
-  int pre_rows;   // rows of one pass (0: fp32 storage)
+  int pre_rows;   // rows of one pass (0: none, prompts run nine positions per pass)
   size_t total;
   // element offsets inside the weight region
   size_t tok_emb, pos_emb, lnf_g, lnf_b, hproj_w, hproj_b, mask, dlnf_g, dlnf_b;
@@ -117,6 +117,7 @@ struct Handle {
   size_t transient_bytes() const { return lay.lncd - lay.a_d16; }
 };
 
-int compute_layout(const wf_config& c, Layout& L);
+// many_rows: with the buffers of the many-row prompt pass (bf16 storage)
+int compute_layout(const wf_config& c, Layout& L, bool many_rows = true);
 
 }  // namespace wf

@@ -115,3 +115,35 @@ def test_profile_names_the_prompt_pass(lens):
         assert prof.get(role, {}).get("launches", 0) >= n and prof[role]["exec_ms"] > 0, (role, prof.get(role))
         if lens != [9] and role not in ("layernorm", "attn_cross"):
             assert prof[role]["launches"] == n, (role, prof[role])
+
+
+@pytest.mark.parametrize("batch,without", [(1, 8176896), (3, 9789696)])
+def test_workspace_without_the_prompt_pass(batch, without, monkeypatch):
+    """A workspace that lacks only the many-row pass's buffers (its size before there was
+    one) is accepted and runs prompts nine positions per pass; one byte less is not."""
+    import ctypes
+    from paper_2609_32869_amd import WfError, binding, load_library
+    lib = load_library()
+
+    class Library:
+        size = without
+
+        def __getattr__(self, name):
+            return getattr(lib, name)
+
+        def wf_workspace_bytes(self, cfg, out):
+            assert lib.wf_workspace_bytes(cfg, out) == 0
+            out._obj.value = min(out._obj.value, self.size)
+            return 0
+
+    cfg = MICRO.with_(dtype="bf16")
+    full = ctypes.c_size_t()
+    ccfg = binding.make_config(cfg, batch)
+    assert lib.wf_workspace_bytes(ctypes.byref(ccfg), ctypes.byref(full)) == 0 and full.value > without
+    small = Library()
+    monkeypatch.setattr(binding, "load_library", lambda: small)
+    ls = _run(cfg, [40, 23, 31][:batch], TOL_MICRO)
+    ls.close()
+    small.size = without - 1
+    with pytest.raises(WfError, match="workspace too small"):
+        binding.WhisperFlash(cfg, batch, [torch.zeros(1, device="cuda")] * len(make_weights(cfg).order))
