@@ -316,16 +316,17 @@ int wf_encoder_workspace_bytes(const wf_encoder_config* cfg, size_t* bytes);
  * mlp.fc2.b; then ln_post.g/b. */
 int wf_encoder_weight_count(const wf_encoder_config* cfg, int* n);
 int wf_encoder_weight_numel(const wf_encoder_config* cfg, int i, int64_t* numel);
-/* Create an encoder over `workspace` (device, 256-byte aligned, >= the bytes
- * above) and copy the bf16 parameters (device pointers in manifest order) into
+/* Create an encoder over `workspace` (device, 256-byte aligned, of the bytes above, or
+ * fewer: down to one request's activations, whose requests then run one after another;
+ * large-v3: 1543 MB, for one request 1343 MB) and copy the bf16 parameters (device pointers in manifest order) into
  * it; the caller's tensors may be freed once `stream` has synchronised.
  * Errors: WF_EINVAL, WF_ESIZE, WF_EHIP. */
 int wf_encoder_init(wf_encoder** e, const wf_encoder_config* cfg, const void* const* weights, int n_weights,
                     void* workspace, size_t ws_bytes, void* stream);
 /* Encode n waveforms: audio device fp32 [n, 2 * n_ctx * hop]; mem device bf16
  * [n, n_ctx, d_model] (16-byte aligned), ready for wf_encode_memory_set.
- * Up to four requests go through the layers together, more in several passes on
- * `stream`. */
+ * Up to four requests (as many as the workspace holds) go through the layers
+ * together, more in several passes on `stream`. */
 int wf_encoder_run(wf_encoder* e, int n, const float* audio, void* mem, void* stream);
 /* The frontend alone: scaled log-mel features of one waveform into mel, device
  * fp32 [n_mels, 2 * n_ctx]. */

@@ -27,6 +27,7 @@ struct EncLayer {
 
 struct EncLayout {
   int T, Tp, Kp1, nb;  // mel frames, positions padded to 64, first-conv row length, FFT bins
+  int batch, pitch;    // requests that one pass of the layers runs, rows from one to the next
   // bf16 weight element offsets
   size_t conv1, conv1_b, conv2, conv2_b, lnp_g, lnp_b, wtotal;
   std::vector<EncLayer> layers;
@@ -34,9 +35,10 @@ struct EncLayout {
   size_t weights, pos, window, twiddle, filters, fband, gmax, logmel, rows1, z, rows2, x, a, qk, vt, o, u, total;
 };
 
-// Requests that one pass of the layers runs together (the workspace holds their
-// activations: 65 MB each at large-v3 shapes).  Their rows lie Tp apart, a multiple of
-// the products' row tiles, so one request costs the same as before.
+// Requests that one pass of the layers runs together at most (the workspace holds their
+// activations: 67 MB each at large-v3 shapes).  Their rows lie Tp apart, so that each
+// request's transposed values start at a multiple of 64 frames; a row tile of 128 or 256
+// may hold two requests.  A workspace for one request has its rows alone.
 constexpr int kEncBatch = 4;
 
 struct Enc {
@@ -72,10 +74,12 @@ int check(const wf_encoder_config* c, std::string& why) {
   return WF_OK;
 }
 
-void layout(const wf_encoder_config& c, EncLayout& L) {
+void layout(const wf_encoder_config& c, EncLayout& L, int batch = kEncBatch) {
   const size_t d = c.d_model, F = c.d_ff;
   L.T = 2 * c.n_ctx;
   L.Tp = (int)up(c.n_ctx, 64);
+  L.batch = batch;
+  L.pitch = batch > 1 ? L.Tp : c.n_ctx;
   L.Kp1 = (int)up(3 * (size_t)c.n_mels, kMmK);
   L.nb = c.n_fft / 2 + 1;
   size_t w = 0;
@@ -104,19 +108,21 @@ void layout(const wf_encoder_config& c, EncLayout& L) {
   L.twiddle = region((size_t)c.n_fft * 16);
   L.filters = region((size_t)c.n_mels * L.nb * 8);
   L.fband = region((size_t)c.n_mels * 8);
-  const size_t R = kEncBatch, Tp = L.Tp;
+  const size_t R = batch, Tp = L.Tp, P = L.pitch;
   L.gmax = region(R * 4);
   L.logmel = region(R * T * c.n_mels * 4);
   L.rows1 = region(R * T * L.Kp1 * 2);
   L.z = region(R * T * d * 2);
   L.rows2 = region(R * n * 3 * d * 2);
-  L.qk = region(R * Tp * 2 * d * 2);
+  L.qk = region(R * P * 2 * d * 2);
   L.vt = region(R * H * kHeadDim * Tp * 2);
-  L.u = region(R * Tp * F * 2);
-  // x, a and o last: the rows between requests are zero from set-up on
-  L.x = region(R * Tp * d * 4);
-  L.a = region(R * Tp * d * 2);
-  L.o = region(R * Tp * d * 2);
+  L.u = region(R * P * F * 2);
+  // x, a and o last, zero at set-up.  The rows between requests stay zero in a and o; in x
+  // the residual products add their bias and more to them in every layer of every call, and
+  // nothing reads them
+  L.x = region(R * P * d * 4);
+  L.a = region(R * P * d * 2);
+  L.o = region(R * P * d * 2);
   L.total = o;
 }
 
@@ -238,6 +244,7 @@ int wf_encoder_init(wf_encoder** out, const wf_encoder_config* cfg, const void* 
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255)) return efail(nullptr, WF_EINVAL, "workspace must be 256-byte aligned");
   EncLayout L;
   layout(*cfg, L);
+  for (int batch = kEncBatch - 1; ws_bytes < L.total && batch > 0; --batch) layout(*cfg, L, batch);
   if (ws_bytes < L.total) return efail(nullptr, WF_ESIZE, "workspace too small");
   auto man = manifest(*cfg, L);
   if (!weights || n_weights != (int)man.size()) return efail(nullptr, WF_EINVAL, "weight count does not match the manifest");
@@ -314,12 +321,12 @@ static MmArgs mm_args(const bf16* A, long long lda, const bf16* B, long long ldb
   return a;
 }
 
-// Waveforms -> acoustic memory [nreq][n_ctx][d] (bf16), nreq <= kEncBatch: the requests'
-// rows stand Tp apart and go through every product of the layers together.
+// Waveforms -> acoustic memory [nreq][n_ctx][d] (bf16), nreq <= L.batch: the requests'
+// rows stand `pitch` apart and go through every product of the layers together.
 static void enc_forward(Enc& e, int nreq, const float* audio, bf16* mem, hipStream_t st) {
   const wf_encoder_config& c = e.cfg;
   const EncLayout& L = e.lay;
-  const int d = c.d_model, F = c.d_ff, H = c.n_head, n = c.n_ctx, Tp = L.Tp, M = nreq * Tp;
+  const int d = c.d_model, F = c.d_ff, H = c.n_head, n = c.n_ctx, Tp = L.Tp, P = L.pitch, M = nreq * P;
   enc_frontend(e, nreq, audio, nullptr, st);
   bf16 *z = e.at<bf16>(L.z), *rows2 = e.at<bf16>(L.rows2), *a = e.at<bf16>(L.a), *qk = e.at<bf16>(L.qk);
   bf16 *vt = e.at<bf16>(L.vt), *o = e.at<bf16>(L.o), *u = e.at<bf16>(L.u);
@@ -330,34 +337,35 @@ static void enc_forward(Enc& e, int nreq, const float* audio, bf16* mem, hipStre
   {
     MmArgs m = mm_args(rows2, 3 * d, e.W(L.conv2), 3 * d, e.W(L.conv2_b), n, d, 3 * d, x, d);
     m.sA = (long long)n * 3 * d;
-    m.sO = (long long)Tp * d;
+    m.sO = (long long)P * d;
     m.add = e.at<float>(L.pos);
     m.ldadd = d;
     mm(m, MM_GELU_ADD_F32, nreq, st);
   }
   for (const EncLayer& w : L.layers) {
-    ln_rows(x, e.W(w.ln1_g), e.W(w.ln1_b), a, n, d, nreq, Tp, Tp, st);
+    ln_rows(x, e.W(w.ln1_g), e.W(w.ln1_b), a, n, d, nreq, P, P, st);
     {  // q | k row-major, v transposed per head [head][dim][Tp]
       MmArgs m = mm_args(a, d, e.W(w.wqkv), d, e.W(w.bqkv), M, 3 * d, d, qk, 2 * d);
       m.out2 = vt;
       m.sO2 = (long long)d * Tp;
       m.d = d;
       m.n_head = H;
-      m.vt_frames = m.period = Tp;
+      m.vt_frames = Tp;
+      m.period = L.batch > 1 ? Tp : 0;
       mm(m, MM_QKV_ENC, 1, st);
     }
     {  // softmax(q k^T / 8) v per head, fused (scores stay on chip)
       EncAttnArgs at{};
       at.qk = qk; at.ldqk = 2 * d; at.vt = vt; at.Tp = Tp; at.o = o; at.ldo = d; at.n = n; at.d = d;
-      at.nreq = nreq; at.sqk = (long long)Tp * 2 * d; at.svt = (long long)d * Tp; at.so = (long long)Tp * d;
+      at.nreq = nreq; at.sqk = (long long)P * 2 * d; at.svt = (long long)d * Tp; at.so = (long long)P * d;
       enc_attention(at, H, st);
     }
     mm(mm_args(o, d, e.W(w.wo), d, e.W(w.bo), M, d, d, x, d), MM_RESID, 1, st);
-    ln_rows(x, e.W(w.ln2_g), e.W(w.ln2_b), a, n, d, nreq, Tp, Tp, st);
+    ln_rows(x, e.W(w.ln2_g), e.W(w.ln2_b), a, n, d, nreq, P, P, st);
     mm(mm_args(a, d, e.W(w.w1), d, e.W(w.b1), M, F, d, u, F), MM_BF16_GELU, 1, st);
     mm(mm_args(u, F, e.W(w.w2), F, e.W(w.b2), M, d, F, x, d), MM_RESID, 1, st);
   }
-  ln_rows(x, e.W(L.lnp_g), e.W(L.lnp_b), mem, n, d, nreq, Tp, n, st);
+  ln_rows(x, e.W(L.lnp_g), e.W(L.lnp_b), mem, n, d, nreq, P, n, st);
 }
 
 int wf_encoder_run(wf_encoder* h, int n, const float* audio, void* mem, void* stream) {
@@ -367,8 +375,8 @@ int wf_encoder_run(wf_encoder* h, int n, const float* audio, void* mem, void* st
   if (reinterpret_cast<uintptr_t>(mem) & 15) return efail(&e, WF_EINVAL, "memory output must be 16-byte aligned");
   hipStream_t st = static_cast<hipStream_t>(stream);
   const size_t ns = (size_t)e.lay.T * e.cfg.hop, per = (size_t)e.cfg.n_ctx * e.cfg.d_model;
-  // passes of at most kEncBatch requests, as even as they come
-  const int npass = (n + kEncBatch - 1) / kEncBatch, each = (n + npass - 1) / npass;
+  // passes of at most lay.batch requests, as even as they come
+  const int npass = (n + e.lay.batch - 1) / e.lay.batch, each = (n + npass - 1) / npass;
   for (int r = 0; r < n; r += each)
     enc_forward(e, std::min(each, n - r), audio + r * ns, static_cast<bf16*>(mem) + r * per, st);
   hipError_t err = hipGetLastError();

@@ -50,6 +50,34 @@ def test_requests_share_a_pass(n):
     encode_and_compare(MICRO_ENC.with_(name="enc-batch", n_ctx=50), n)
 
 
+@pytest.mark.parametrize("n_ctx,size", [(48, 1114880), (50, 1125888), (50, 1600000)])
+def test_encoder_workspace_for_fewer_requests(n_ctx, size, monkeypatch):
+    """Three requests in a workspace for one (its size before requests shared a pass; one byte
+    less is refused) and for two."""
+    from paper_2609_32869_amd import WfError, WhisperEncoder, binding, load_library
+    lib = load_library()
+
+    class Library:
+        bytes = size
+
+        def __getattr__(self, name):
+            return getattr(lib, name)
+
+        def wf_encoder_workspace_bytes(self, cfg, out):
+            assert lib.wf_encoder_workspace_bytes(cfg, out) == 0 and out._obj.value > self.bytes
+            out._obj.value = self.bytes
+            return 0
+
+    ecfg = MICRO_ENC.with_(name="enc-small", n_ctx=n_ctx)
+    small = Library()
+    monkeypatch.setattr(binding, "load_library", lambda: small)
+    encode_and_compare(ecfg, 3)
+    if size < 1200000:
+        small.bytes = size - 1
+        with pytest.raises(WfError, match="workspace too small"):
+            WhisperEncoder(ecfg, [torch.zeros(1, device="cuda")] * len(make_encoder_weights(ecfg).order))
+
+
 @pytest.mark.parametrize("n_frames", [300, 256])
 def test_acoustic_keys_and_values_of_many_blocks(n_frames):
     """Twelve blocks' keys and transposed values in one launch: rows that end inside a
