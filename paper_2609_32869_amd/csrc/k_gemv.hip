@@ -1293,7 +1293,7 @@ template <int EPI>
 static void launch_gemm(const GemvArgs& a, hipStream_t st) {
   const int mb0 = a.slot0 * kRows / 64, mb1 = ((a.slot0 + a.nslots) * kRows + 63) / 64;
   const int nmb = mb1 - mb0, ks = a.ksplit > 1 ? a.ksplit : 1;
-  const int nnb = (a.N + 63) / 64, rs = xcd_row_parts(nmb, (size_t)64 * (a.K / ks) * 4);
+  const int nnb = (a.N + 63) / 64, rs = xcd_row_parts(nmb, nnb, (size_t)64 * (a.K / ks) * 4);
   k_gemm<EPI><<<dim3(xcd_blocks(nmb, nnb, rs) + pf_blocks(a), ks), 256, 0, st>>>(a, mb0, nmb, nnb, rs);
 }
 

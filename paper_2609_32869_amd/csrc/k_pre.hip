@@ -469,7 +469,7 @@ namespace {
 template <int EPI, int P, int WK, int TI, int TJ, int D>
 void gemm_launch(const PreGemmArgs& a, int ks, hipStream_t st) {
   const int nmb = (a.M + 32 * TI - 1) / (32 * TI), nnb = (a.N + 32 * TJ - 1) / (32 * TJ);
-  const int rs = xcd_row_parts(nmb, (size_t)32 * TI * (a.K / ks) * 2 * P);
+  const int rs = xcd_row_parts(nmb, nnb, (size_t)32 * TI * (a.K / ks) * 2 * P);
   k_pre_gemm<EPI, P, WK, TI, TJ, D><<<dim3(xcd_blocks(nmb, nnb, rs), ks), 256, 0, st>>>(a, nmb, nnb, rs);
 }
 int blocks_of(const PreGemmArgs& a, int ti, int tj) {

@@ -373,7 +373,6 @@ constexpr int kPrePart = 16;
 static_assert(kPrePart == kPage, "a part's keys and values fill one cache page");
 constexpr int kPreMaxRows = 2048;  // rows of one pass (more parts: several passes)
 constexpr int kPreMaxSplit = 4;    // k-splits of a product that leaves partial sums
-constexpr size_t kPreXcdRowBytes = (size_t)5 << 19;  // operand bytes one XCD's blocks share at most (L2: 4 MB)
 constexpr int kPreCus = 256;       // compute units: blocks of one round
 struct PrePart {
   int slot, pos0, nv, last;  // nv valid rows; last: the prompt's last part

@@ -3,11 +3,12 @@
 #pragma once
 #include "wf_kernels.h"
 #include "wf_operand.h"
+#include "wf_split.h"
 
 namespace wf {
 
-// XCD x (block % 8) takes row part x % rs of rs and column part x / rs of 8 / rs, row
-// blocks fastest; false for a block past the grid of tiles.
+// The tile of this block (xcd_blocks, wf_split.h: XCD x = block % 8); false for a block past
+// the grid of tiles.
 __device__ __forceinline__ bool xcd_tile(int nmb, int nnb, int rs, int& mbk, int& nbk) {
   const int x = blockIdx.x & 7, bi = blockIdx.x >> 3;
   const int nrh = (nmb + rs - 1) / rs, ncq = (nnb * rs + 7) / 8;
@@ -15,15 +16,6 @@ __device__ __forceinline__ bool xcd_tile(int nmb, int nnb, int rs, int& mbk, int
   nbk = (x / rs) * ncq + bi / nrh;
   return mbk < nmb && bi / nrh < ncq && nbk < nnb;
 }
-// Row parts so that the operand rows of one XCD's blocks stay in its L2 (4 MB) while the
-// weights pass by: 1776 two-plane rows, K = 1280, 5120 columns 90 us with all rows per
-// XCD, 65, 60 and 68 with half, a quarter and an eighth; 864 rows 37, 33, 34 and 35.
-inline int xcd_row_parts(int nmb, size_t block_bytes) {
-  int rs = 1;
-  while (rs < 8 && (size_t)((nmb + rs - 1) / rs) * block_bytes > kPreXcdRowBytes) rs *= 2;
-  return rs;
-}
-inline unsigned xcd_blocks(int nmb, int nnb, int rs) { return 8u * ((nmb + rs - 1) / rs) * ((nnb * rs + 7) / 8); }
 
 // Rows 8 (lane / 32) .. + 7 of half `half` (16 rows) of a 32 x 32 accumulator, this lane's
 // column, + bias, as eight bf16: the two row groups change places between half-waves.
