@@ -20,6 +20,7 @@
 #include "wf_common.h"
 #include "wf_kernels.h"
 #include "wf_operand.h"
+#include "wf_split.h"
 
 namespace wf {
 
@@ -211,7 +212,7 @@ __global__ void __launch_bounds__(NT) k_mm(MmArgs a, int nmb, int nnb, int rs) {
       if (EP == MM_XKV) {
         bf16* vt = out + (size_t)a.n_head * a.M * kHeadDim + (size_t)head * kHeadDim * a.vt_frames;
         *reinterpret_cast<uint4*>(vt + vt_index(dim, f)) = pk;
-      } else {  // the tile's rows belong to one request
+      } else {  // a tile may hold rows of two requests, eight frames from a multiple of 8 are one's
         const int req = a.period > 0 ? f / a.period : 0;
         bf16* vt = reinterpret_cast<bf16*>(a.out2) + (size_t)(z + req) * a.sO2;
         *reinterpret_cast<uint4*>(vt + ((size_t)head * kHeadDim + dim) * a.vt_frames + f - req * a.period) = pk;
@@ -418,7 +419,7 @@ __global__ void __launch_bounds__(512, 2) k_mmw(MmArgs a, int nmb, int nnb, int 
             bf16* vt = reinterpret_cast<bf16*>(a.out) + (size_t)z * a.sO + (size_t)a.n_head * a.M * kHeadDim +
                        (size_t)head * kHeadDim * a.vt_frames;
             *reinterpret_cast<uint4*>(vt + vt_index(dim, f)) = pk;
-          } else {
+          } else {  // as in k_mm
             const int req = a.period > 0 ? f / a.period : 0;
             bf16* vt = reinterpret_cast<bf16*>(a.out2) + (size_t)(z + req) * a.sO2;
             *reinterpret_cast<uint4*>(vt + ((size_t)head * kHeadDim + dim) * a.vt_frames + f - req * a.period) = pk;
@@ -447,32 +448,7 @@ int mm_check(const MmArgs& a, int ep) {
 }
 
 namespace {
-// Blocks of a launch over the XCDs: row part x % rs of rs, column part x / rs of 8 / rs.
-// The split with the fewest rounds of blocks per XCD (32 CUs of `occ` blocks), then
-// the one whose blocks share the fewest rows and columns: 6144 rows, K = 5120, N =
-// 1280 on 256 x 128 tiles 148, 137 and 76 us with 1, 2 and 4 row parts (48, 36 and 30
-// blocks per XCD).
-struct XcdSplit {
-  int nmb, nnb, rs;
-  long long rounds;
-};
-XcdSplit xcd_split(int rows, int cols, int bm, int bn, int occ, int batch) {
-  XcdSplit best{(rows + bm - 1) / bm, (cols + bn - 1) / bn, 1, 0};
-  long long least = 0;
-  for (int rs = 1; rs <= 8; rs *= 2) {
-    const int nrh = (best.nmb + rs - 1) / rs, ncq = (best.nnb * rs + 7) / 8;
-    const long long rounds = ((long long)nrh * ncq * batch + 32 * occ - 1) / (32 * occ), share = (long long)nrh * bm + (long long)ncq * bn;
-    if (rs == 1 || rounds < best.rounds || (rounds == best.rounds && share < least)) {
-      best.rounds = rounds;
-      best.rs = rs;
-      least = share;
-    }
-  }
-  return best;
-}
-dim3 xcd_grid(const XcdSplit& x, int batch) {
-  return dim3(8u * ((x.nmb + x.rs - 1) / x.rs) * ((x.nnb * x.rs + 7) / 8), 1, batch);
-}
+dim3 xcd_grid(const XcdSplit& x, int batch) { return dim3(xcd_blocks(x.nmb, x.nnb, x.rs), 1, batch); }
 }  // namespace
 
 template <int BM, int NS>
@@ -501,18 +477,12 @@ static void mmw_launch(const MmArgs& a, int ep, const XcdSplit& x, int batch, hi
   }
 }
 
-// The tile with the least time: rounds of blocks times what a round of 1280 columns of
-// k takes (256 x 128 tiles, one block per CU, 27 us; 128 x 128 in two stages, two per
-// CU, 29; 64 x 128 in four stages, one per CU, 12).  1500 rows: 5120 columns 27, 29
-// and 54 us, 3840 columns 21, 27 and 37, 1280 columns 22, 21 and 10.
 void mm(const MmArgs& a, int ep, int batch, hipStream_t st) {
   const int rows = std::max(a.M, (ep == MM_XKV || ep == MM_QKV_ENC) ? a.vt_frames : a.M);
-  const XcdSplit w = xcd_split(rows, a.N, 256, BN, 1, batch), m = xcd_split(rows, a.N, 128, BN, 2, batch),
-                 n = xcd_split(rows, a.N, 64, BN, 1, batch);
-  const long long tw = 27 * w.rounds, tm = 29 * m.rounds, tn = 12 * n.rounds;
-  if (tw <= tm && tw <= tn) mmw_launch(a, ep, w, batch, st);
-  else if (tm <= tn) mm_launch<128, 2>(a, ep, m, batch, st);
-  else mm_launch<64, 4>(a, ep, n, batch, st);
+  const MmTile t = mm_tile(rows, a.N, BN, batch);
+  if (t.rows == 256) mmw_launch(a, ep, t.split, batch, st);
+  else if (t.rows == 128) mm_launch<128, 2>(a, ep, t.split, batch, st);
+  else mm_launch<64, 4>(a, ep, t.split, batch, st);
 }
 
 }  // namespace wf

@@ -1,11 +1,12 @@
-// How a launch's tiles are spread over the chip's eight XCDs (internal; host rules, no device
-// code).
+// How a launch's tiles are spread over the chip's eight XCDs, and which tile a request-time
+// product takes (internal; host rules, no device code).
 #pragma once
 #include <cstddef>
 
 namespace wf {
 
 constexpr int kXcds = 8;
+constexpr int kXcdCus = 32;  // compute units of one XCD
 constexpr size_t kXcdRowBytes = (size_t)5 << 19;  // operand bytes one XCD's blocks share at most (L2: 4 MB)
 
 // nmb x nnb tiles: XCD x takes row part x % rs of rs and column part x / rs of 8 / rs, row
@@ -27,6 +28,48 @@ inline int xcd_row_parts(int nmb, int nnb, size_t block_bytes) {
          8 * xcd_most_blocks(nmb, nnb, 2 * rs) <= 9 * xcd_most_blocks(nmb, nnb, rs))
     rs *= 2;
   return rs;
+}
+
+// Request-time products: the split with the fewest rounds of blocks per XCD (32 CUs of `occ`
+// blocks), then the one whose blocks share the fewest rows and columns: 6144 rows, K = 5120,
+// N = 1280 on 256 x 128 tiles 148, 137 and 76 us with 1, 2 and 4 row parts (48, 36 and 30
+// blocks per XCD).
+struct XcdSplit {
+  int nmb, nnb, rs;
+  long long rounds;
+};
+inline XcdSplit xcd_split(int rows, int cols, int bm, int bn, int occ, int batch) {
+  XcdSplit best{(rows + bm - 1) / bm, (cols + bn - 1) / bn, 1, 0};
+  long long least = 0;
+  for (int rs = 1; rs <= kXcds; rs *= 2) {
+    const long long nrh = (best.nmb + rs - 1) / rs, ncq = (best.nnb * rs + kXcds - 1) / kXcds;
+    const long long rounds = (nrh * ncq * batch + kXcdCus * occ - 1) / (kXcdCus * occ), share = nrh * bm + ncq * bn;
+    if (rs == 1 || rounds < best.rounds || (rounds == best.rounds && share < least)) {
+      best.rounds = rounds;
+      best.rs = rs;
+      least = share;
+    }
+  }
+  return best;
+}
+
+// The tile with the least time: rounds of blocks times what a round of 1280 columns of
+// k takes (256 x 128 tiles, one block per CU, 27 us; 128 x 128 in two stages, two per
+// CU, 29; 64 x 128 in four stages, one per CU, 12).  1500 rows: 5120 columns 27, 29
+// and 54 us, 3840 columns 21, 27 and 37, 1280 columns 22, 21 and 10.  For short rows
+// and half-filled rounds the three lie closer than that: over the encoder's products of widths
+// 512, 768 and 1280 for one to four requests the tile taken is the fastest of the three or
+// within 10% of it in five of six, 24% at most with K >= 768 or over 1536 rows and 31% below
+// that (1024 columns, K = 512, two matrices 15.5 us, 11.9 on 256 x 128 tiles).
+struct MmTile {
+  int rows;  // 256, 128 or 64
+  XcdSplit split;
+};
+inline MmTile mm_tile(int rows, int cols, int bn, int batch) {
+  const XcdSplit w = xcd_split(rows, cols, 256, bn, 1, batch), m = xcd_split(rows, cols, 128, bn, 2, batch),
+                 n = xcd_split(rows, cols, 64, bn, 1, batch);
+  const long long tw = 27 * w.rounds, tm = 29 * m.rounds, tn = 12 * n.rounds;
+  return tw <= tm && tw <= tn ? MmTile{256, w} : tm <= tn ? MmTile{128, m} : MmTile{64, n};
 }
 
 }  // namespace wf

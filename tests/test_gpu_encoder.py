@@ -2,9 +2,7 @@
 
   * the log-mel frontend (fp64 on both sides) agrees to 1e-5;
   * the acoustic memory agrees with the oracle computed with the same bf16
-    rounding of every product input (fp32 accumulation on both sides; the
-    difference comes from accumulation order flipping bf16 roundings of
-    intermediate values), at micro and large-v3 shapes;
+    rounding of every product input (encoder_check.py), at micro and large-v3 shapes;
   * end to end: waveform -> GPU encoder -> wf_encode_memory_set -> prefill ->
     draft + verify steps, against the oracle decoding from its own encoder
     output (logits within the decoder's bf16 tolerance, tokens identical
@@ -14,6 +12,7 @@ import numpy as np
 import pytest
 import torch
 
+from encoder_check import encode_and_compare
 from wf_fixtures import (MICRO, MICRO_ENC, LARGE_V3_ENC, make_encoder_weights, make_audio, make_weights,
                          make_prefix)
 from oracle import OracleOpts
@@ -23,10 +22,6 @@ from oracle.numerics import bf16
 pytestmark = pytest.mark.gpu
 
 ENC_OPTS = OracleOpts(dtype=np.float32, gemm_bf16=True, exact=False)
-# acoustic memory: unit-scale LayerNorm output stored in bf16, whose ulp is 2^-7 = 7.8e-3
-# for |A| in [1, 2): any element may differ by one stored ulp where an accumulation
-# order flipped a rounding; the mean stays far below it
-TOL_MEM_MAX, TOL_MEM_MEAN = 8e-3, 5e-4
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -53,27 +48,13 @@ def test_logmel_frontend():
     enc.close()
 
 
-def _compare_memory(ecfg, nreq):
-    enc, W = _encoder(ecfg)
-    audio = np.stack([make_audio(ecfg, s) for s in range(nreq)])
-    got = enc.run(torch.from_numpy(audio).cuda()).float().cpu().numpy()
-    E = Encoder(ecfg, W.values, ENC_OPTS)
-    for s in range(nreq):
-        want = bf16(E.encode(audio[s]))
-        d = np.abs(got[s] - want)
-        print(f"{ecfg.name} request {s}: max |dA| {d.max():.3e}, mean {d.mean():.3e}, "
-              f"share > 1e-2 {np.mean(d > 1e-2):.2e}", flush=True)
-        assert d.max() <= TOL_MEM_MAX and d.mean() <= TOL_MEM_MEAN
-    enc.close()
-
-
 def test_micro_encoder_matches_oracle():
-    _compare_memory(MICRO_ENC, 2)
+    encode_and_compare(MICRO_ENC, 2)
 
 
 @pytest.mark.timeout(900)
 def test_large_v3_encoder_matches_oracle():
-    _compare_memory(LARGE_V3_ENC, 1)
+    encode_and_compare(LARGE_V3_ENC, 1, std=0.02)
 
 
 def test_waveform_to_tokens_micro():

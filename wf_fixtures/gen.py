@@ -50,7 +50,7 @@ class WeightSet:
 
 
 def _is_ln_gain(name):
-    return name.endswith("_ln.g") or name.endswith("ln_f.g")
+    return name.endswith("_ln.g") or name.endswith(("ln_f.g", "ln_post.g"))
 
 
 def _is_drafter(name):
