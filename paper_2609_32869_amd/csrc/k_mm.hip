@@ -71,7 +71,7 @@ __global__ void __launch_bounds__(NT) k_mm(MmArgs a, int nmb, int nnb, int rs) {
   const int m0 = mbk * BM, n0 = nbk * BN;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int wm = w >> 1, wn = w & 1;
-  const int nk = a.K / BK, nbB = a.nb > 0 ? a.nb : a.N;
+  const int nk = a.K / BK;
 
   // this lane's copy sources: LDS chunk slot s = (w * J + j) * 64 + lane holds row
   // s / 8, chunk (s % 8) ^ (row & 7) of the tile (rows past the matrix re-read its
@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(NT) k_mm(MmArgs a, int nmb, int nnb, int rs) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int slot = (w * 4 + j) * 64 + lane, row = slot >> 3, ch = (slot & 7) ^ (row & 7);
-    srcB[j] = B + (size_t)min(n0 + row, nbB - 1) * a.ldb + 8 * ch;
+    srcB[j] = B + (size_t)min(n0 + row, a.N - 1) * a.ldb + 8 * ch;
   }
   auto copy = [&](int kt, uint4* stage) {  // k-step kt (past the last: the last one)
     const int k0 = min(kt, nk - 1) * BK;
@@ -225,7 +225,7 @@ __global__ void __launch_bounds__(NT) k_mm(MmArgs a, int nmb, int nnb, int rs) {
     const int rl = it / (BN / 8), c8 = (it % (BN / 8)) * 8, f = m0 + rl, n = n0 + c8;
     if (f >= a.M || n >= a.N) continue;
     const float* src = ct(rl) + c8;
-    if (EP == MM_BF16 || EP == MM_BF16_GELU) {
+    if (EP == MM_BF16_GELU) {
       bf16* out = reinterpret_cast<bf16*>(a.out) + (size_t)z * a.sO;
       *reinterpret_cast<uint4*>(out + (size_t)f * a.ldo + n) = pack8(src);
     } else {
@@ -276,14 +276,14 @@ __global__ void __launch_bounds__(512, 2) k_mmw(MmArgs a, int nmb, int nnb, int 
   const int m0 = mbk * BM, n0 = nbk * BN;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int wm = w / WC, wn = w % WC, lr = lane & 31, lk = lane >> 5;
-  const int nk = a.K / BK, nbB = a.nb > 0 ? a.nb : a.N;
+  const int nk = a.K / BK;
   // copy sources as in k_mm: slot s holds row s / 8, chunk (s % 8) ^ (row & 7)
   const bf16* src[CPW];
 #pragma unroll
   for (int j = 0; j < CPW; ++j) {
     const bool isA = j < JA;
     const int slot = (w * (isA ? JA : JB) + (isA ? j : j - JA)) * 64 + lane, row = slot >> 3, ch = (slot & 7) ^ (row & 7);
-    src[j] = isA ? A + (size_t)min(m0 + row, a.M - 1) * a.lda + 8 * ch : B + (size_t)min(n0 + row, nbB - 1) * a.ldb + 8 * ch;
+    src[j] = isA ? A + (size_t)min(m0 + row, a.M - 1) * a.lda + 8 * ch : B + (size_t)min(n0 + row, a.N - 1) * a.ldb + 8 * ch;
   }
   auto copy1 = [&](int j, int k0, uint4* stage) {
     __builtin_amdgcn_global_load_lds((const void*)(src[j] + k0),
@@ -364,14 +364,14 @@ __global__ void __launch_bounds__(512, 2) k_mmw(MmArgs a, int nmb, int nnb, int 
         c[v] = c[v] * a.scale + bv;
         if (EP == MM_BF16_GELU || EP == MM_GELU_ADD_F32) c[v] = gelu_erf(c[v]);
       }
-      if (EP == MM_F32 || EP == MM_RESID || EP == MM_GELU_ADD_F32) {
+      if (EP == MM_RESID || EP == MM_GELU_ADD_F32) {
         float* out = reinterpret_cast<float*>(a.out) + (size_t)z * a.sO + nc;
         if (nc < a.N) {
           float o[16];
 #pragma unroll
           for (int v = 0; v < 16; ++v) {  // every load first (rows past the matrix re-read its last one)
             const int f = min(mt + 8 * (v >> 2) + 4 * lk + (v & 3), a.M - 1);
-            o[v] = EP == MM_RESID ? out[(size_t)f * a.ldo] : EP == MM_GELU_ADD_F32 ? a.add[(size_t)f * a.ldadd + nc] : 0.f;
+            o[v] = EP == MM_RESID ? out[(size_t)f * a.ldo] : a.add[(size_t)f * a.ldadd + nc];
           }
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
@@ -436,7 +436,7 @@ __global__ void __launch_bounds__(512, 2) k_mmw(MmArgs a, int nmb, int nnb, int 
 int mm_check(const MmArgs& a, int ep) {
   if (a.M < 1 || a.N < 1 || a.K < kMmK || a.K % kMmK) return -1;
   if (a.N % 8 || a.lda % 8 || a.ldb % 8 || a.lda < a.K || a.ldb < a.K) return -1;
-  if ((ep == MM_BF16 || ep == MM_BF16_GELU || ep == MM_F32 || ep == MM_RESID || ep == MM_GELU_ADD_F32) &&
+  if ((ep == MM_BF16_GELU || ep == MM_RESID || ep == MM_GELU_ADD_F32) &&
       (a.ldo % 8 || a.ldo < a.N))
     return -1;
   if (ep == MM_GELU_ADD_F32 && (!a.add || a.ldadd < a.N)) return -1;
@@ -455,8 +455,6 @@ template <int BM, int NS>
 static void mm_launch(const MmArgs& a, int ep, const XcdSplit& x, int batch, hipStream_t st) {
   const dim3 grid = xcd_grid(x, batch);
   switch (ep) {
-    case MM_F32: k_mm<MM_F32, BM, NS><<<grid, NT, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
-    case MM_BF16: k_mm<MM_BF16, BM, NS><<<grid, NT, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
     case MM_BF16_GELU: k_mm<MM_BF16_GELU, BM, NS><<<grid, NT, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
     case MM_RESID: k_mm<MM_RESID, BM, NS><<<grid, NT, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
     case MM_XKV: k_mm<MM_XKV, BM, NS><<<grid, NT, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
@@ -467,8 +465,6 @@ static void mm_launch(const MmArgs& a, int ep, const XcdSplit& x, int batch, hip
 static void mmw_launch(const MmArgs& a, int ep, const XcdSplit& x, int batch, hipStream_t st) {
   const dim3 grid = xcd_grid(x, batch);
   switch (ep) {
-    case MM_F32: k_mmw<MM_F32><<<grid, 512, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
-    case MM_BF16: k_mmw<MM_BF16><<<grid, 512, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
     case MM_BF16_GELU: k_mmw<MM_BF16_GELU><<<grid, 512, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
     case MM_RESID: k_mmw<MM_RESID><<<grid, 512, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;
     case MM_XKV: k_mmw<MM_XKV><<<grid, 512, 0, st>>>(a, x.nmb, x.nnb, x.rs); break;

@@ -298,8 +298,6 @@ void gemm_xkv(const XkvArgs& a, int nslots, hipStream_t st);
 // sBias, sO, sO2).
 constexpr int kMmTile = 128, kMmK = 64;
 enum {
-  MM_F32 = 0,        // out fp32 [M][ldo] = scale * C + bias
-  MM_BF16 = 1,       // out bf16 [M][ldo]
   MM_BF16_GELU = 2,  // out bf16 [M][ldo] = GELU(scale * C + bias)
   MM_RESID = 3,      // out fp32 [M][ldo] += scale * C + bias
   MM_XKV = 4,        // acoustic keys [head][frame][64] then values [head][frame / 256][dim][256]
@@ -322,7 +320,6 @@ struct MmArgs {
   float scale;
   const float* add;  // MM_GELU_ADD_F32: fp32 rows added after the activation
   long long ldadd;
-  int nb;            // rows of B present (0: N); columns past them re-read its last row
   // MM_QKV_ENC over several requests: rows of one request (a multiple of 64, vt_frames);
   // the values of request r lie r sO2 elements on.  0: one request
   int period;
