@@ -185,7 +185,8 @@ __global__ void __launch_bounds__(NT) k_mm(MmArgs a, int nmb, int nnb, int rs) {
     // columns [0, nrow) row-major bf16 (keys, or queries | keys), columns
     // [nrow, N) values transposed per head: MM_XKV in 256-frame pieces
     // [head][frame / 256][dim][256] after the keys [head][frame][64]; MM_QKV_ENC as
-    // [head][dim][ldv] in out2.  Frames from M to the padded count are zeros.
+    // [head][dim][ldv] in out2.  Frames from M to the padded count are zeros (between
+    // requests, period > 0: what the rows there give).
     const int nrow = EP == MM_XKV ? a.d : 2 * a.d;
     bf16* out = reinterpret_cast<bf16*>(a.out) + (size_t)z * a.sO;
     // row-major part: items (row, 8 columns)

@@ -311,7 +311,11 @@ struct PrePlan {
 
 // Prompts of more nine-row passes than this take the many-row pass, which costs about
 // 4 ms for up to 64 rows at large-v3 shapes: with one slot a nine-row pass takes 1.4 ms
-// (18 tokens 2.9 against 4.0 ms, 27 tokens 4.3 against 3.9), with several 3.4-4.6.
+// (18 tokens 2.8 against 3.9 ms, 27 tokens 4.4 against 3.9), with several 3.2 and more.
+// The same line holds at widths 512 and 768, where both are a third of that and less: one
+// slot, 18 tokens 0.46 and 0.91 ms in nine-row passes, 19 tokens 0.60 and 1.36 in the
+// many-row pass against 0.69 and 1.46 in three; two slots, 10 tokens 0.55 and 1.25
+// against 0.96 and 2.13.
 int pre_min_passes(const Layout& L) { return L.nsplit_op == 3 ? 2 : 1; }
 PrePlan pre_plan(const Handle* h, int slot0, int n, const int32_t* lens, int max_len) {
   PrePlan pl;
@@ -595,7 +599,7 @@ struct Runner {
   // kFc2SplitBatch (partial sums reduced with the residual update and the next
   // LayerNorm), else 0: its few columns alone give too few 64 x 64 tiles.  Split two
   // ways a step of 8, 16 and 96 slots takes 3.56, 4.42 and 12.91 ms, four ways 3.39,
-  // 4.49 and 12.84.
+  // 4.49 and 12.84: four at every batch, 0.07 ms behind at 16 slots.
   int fc2_split_batch() const {
     if (L.nsplit_op != 2) return 0;
     return (c.d_ff / 32) % kFc2SplitBatch == 0 ? kFc2SplitBatch : 0;

@@ -35,11 +35,10 @@ enum { W_ROW = 0, W_F16 = 1, W_F32 = 2 };
 
 // Weights of a later product read ahead by extra blocks of an earlier launch.
 // With many slots every weight product runs from HBM (a step reads far more
-// weights than the memory-side cache holds), and the wide-tile GEMM, which loads
-// its fragments straight into registers four k-steps ahead, stalls on those
-// first reads; read once shortly before, it runs as if warm (864 rows, first MLP
-// product: 41.5 -> 34.0 us standalone).  Non-temporal loads do not allocate in
-// that cache and do not help.
+// weights than the memory-side cache holds), and a product whose waves load their
+// fragments straight into registers stalls on those first reads; read once shortly
+// before, it runs as if warm.  Non-temporal loads do not allocate in that cache and do
+// not help.
 struct Touch {
   const void* p;  // null: nothing to read
   size_t bytes;
@@ -293,8 +292,8 @@ struct XkvArgs {  // fp32; element strides per layer and per slot
 void gemm_xkv(const XkvArgs& a, int nslots, hipStream_t st);
 
 // Request-time matrix-core GEMM (k_mm.hip): C = A B^T (+ bias) for bf16 A [M, K] and
-// B [N, K] (row-major, k contiguous), fp32 accumulation, 128 x 128 tiles, k in steps
-// of kMmK; grid z runs over `batch` independent products (element strides sA, sB,
+// B [N, K] (row-major, k contiguous), fp32 accumulation, tiles of 256, 128 or 64 rows x
+// kMmTile columns, k in steps of kMmK; grid z runs over `batch` independent products (element strides sA, sB,
 // sBias, sO, sO2).
 constexpr int kMmTile = 128, kMmK = 64;
 enum {
@@ -350,8 +349,8 @@ void conv_rows_s2(const bf16* z, bf16* out, int n_in, int n_out, int d, int nreq
 void ln_rows(const float* x, const bf16* g, const bf16* b, bf16* out, int rows, int d, int nreq, int in_period,
              int out_period, hipStream_t st);
 // fused bidirectional attention of the encoder: q | k rows [n][ldqk] (q at column
-// head * 64, k at d + head * 64), values transposed per head [head][64][Tp] (zero
-// past n), output rows [n][ldo] at column head * 64; Tp a multiple of 64
+// head * 64, k at d + head * 64), values transposed per head [head][64][Tp] (finite
+// past n, where the probabilities are zero), output rows [n][ldo] at column head * 64; Tp a multiple of 64
 struct EncAttnArgs {
   const bf16* qk;
   int ldqk;

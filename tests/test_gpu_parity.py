@@ -195,9 +195,10 @@ def test_micro_bf16_b3_two_plane_operands():
 def test_micro_bf16_b64_wide_tiles():
     """64 slots (576 rows, nine 64-row blocks), bf16, d 1024 (16 heads), FFN 2560:
     the q|k|v (3072 columns, k/v appended to the paged cache), first MLP (2560
-    columns, GELU into the next operand) and drafter q|k|v products take the
-    wide-tile kernel on the 32x32x16 matrix instruction (operand rows read from
-    16x32 fragment order); ragged prompts, planted drafts on six followed slots."""
+    columns, GELU into the next operand) and drafter q|k|v products on 64 x 64 tiles
+    whose waves split k (operand rows read from 16x32 fragment order), the row blocks
+    in one to four parts over the XCDs; ragged prompts, planted drafts on six followed
+    slots."""
     from lockstep import Lockstep
     cfg = MICRO_BF16.with_(name="micro-wide", d_model=1024, n_head=16, d_ff=2560)
     W = make_weights(cfg)
@@ -250,9 +251,8 @@ def test_micro_bf16_b64_cross_attention_by_pair(frames):
 @pytest.mark.timeout(900)
 def test_micro_bf16_b96_width1280_all_slots():
     """96 slots (864 rows) at width 1280 (20 heads), FFN 5120, two blocks: the
-    1280-column products take the LDS-staged 64 x 64 GEMM with 280 tile blocks,
-    and W'_o and W_2 append blocks that read the next wide-tile product's weights
-    (W_1, the next block's q|k|v) ahead.  Every slot is compared with the oracle,
+    1280-column products take 280 tile blocks (unsplit), and W'_o and W_2 append
+    blocks that read the next product's weights (W_1, the next block's q|k|v) ahead.  Every slot is compared with the oracle,
     so a tile block lost to the appended ones would show in some slot's logits."""
     from lockstep import Lockstep
     cfg = MICRO_BF16.with_(name="micro-1280", d_model=1280, n_head=20, d_ff=5120)
@@ -272,8 +272,7 @@ def test_micro_bf16_b96_width1280_all_slots():
 
 def test_bf16_b96_width768_all_slots():
     """96 slots at width 768 (12 heads), FFN 3072, 700 frames, two blocks: the
-    first MLP product takes the wide-tile kernel with 256-column tiles (3072 is
-    not a multiple of 320), q|k|v (2304 columns) the LDS-staged 64 x 64 GEMM,
+    products' column blocks are not whole multiples of the XCDs' parts (36, 12 and 48),
     the read-ahead blocks carry those widths, and the cross-attention runs one
     block per (head, slot) over six 128-frame chunks, the last one ragged (60
     frames).  Every slot is compared with the oracle."""
