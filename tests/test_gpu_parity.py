@@ -197,7 +197,7 @@ def test_micro_bf16_b64_wide_tiles():
     the q|k|v (3072 columns, k/v appended to the paged cache), first MLP (2560
     columns, GELU into the next operand) and drafter q|k|v products on 64 x 64 tiles
     whose waves split k (operand rows read from 16x32 fragment order), the row blocks
-    in one to four parts over the XCDs; ragged prompts, planted drafts on six followed
+    in one part or two over the XCDs; ragged prompts, planted drafts on six followed
     slots."""
     from lockstep import Lockstep
     cfg = MICRO_BF16.with_(name="micro-wide", d_model=1024, n_head=16, d_ff=2560)
@@ -272,7 +272,7 @@ def test_micro_bf16_b96_width1280_all_slots():
 
 def test_bf16_b96_width768_all_slots():
     """96 slots at width 768 (12 heads), FFN 3072, 700 frames, two blocks: the
-    products' column blocks are not whole multiples of the XCDs' parts (36, 12 and 48),
+    products of 36, 12 and 48 column blocks in four parts over the XCDs, the row blocks in two,
     the read-ahead blocks carry those widths, and the cross-attention runs one
     block per (head, slot) over six 128-frame chunks, the last one ragged (60
     frames).  Every slot is compared with the oracle."""
