@@ -57,10 +57,10 @@ inline XcdSplit xcd_split(int rows, int cols, int bm, int bn, int occ, int batch
 // k takes (256 x 128 tiles, one block per CU, 27 us; 128 x 128 in two stages, two per
 // CU, 29; 64 x 128 in four stages, one per CU, 12).  1500 rows: 5120 columns 27, 29
 // and 54 us, 3840 columns 21, 27 and 37, 1280 columns 22, 21 and 10.  For short rows
-// and half-filled rounds the three lie closer than that: over the encoder's products of widths
-// 512, 768 and 1280 for one to four requests the tile taken is the fastest of the three or
-// within 10% of it in five of six, 24% at most with K >= 768 or over 1536 rows and 31% below
-// that (1024 columns, K = 512, two matrices 15.5 us, 11.9 on 256 x 128 tiles).
+// and half-filled rounds the three lie closer than that: over the request-time products of
+// widths 512, 768 and 1280 for one to four requests the tile taken is the fastest of the
+// three or within 10% of it in five of six, and 31% behind at most (1500 rows, 1024
+// columns, K = 512, two matrices 15.5 us, 11.9 on 256 x 128 tiles).
 struct MmTile {
   int rows;  // 256, 128 or 64
   XcdSplit split;
