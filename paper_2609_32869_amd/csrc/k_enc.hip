@@ -210,10 +210,10 @@ __global__ void __launch_bounds__(256) k_ln_rows(const float* __restrict__ x, co
 // transposed values stream through four LDS stages in tiles of 64 keys, copied
 // straight from memory (global_load_lds_dwordx4) three tiles ahead of their use.
 // Per 32 keys a wave forms S^T = K q^T on v_mfma_f32_32x32x16_bf16, so a lane holds 16
-// keys of one query: the running maximum and sum are per lane (one swap of
-// half-waves joins a query's two lanes), p = exp(s - m) is rounded to bf16 in place
+// keys of one query: the reference of its scores (near their maximum) and the sum are per
+// lane (one swap of half-waves joins a query's two lanes), p is rounded to bf16 in place
 // and two half-wave swaps of the packed pairs make it the B operand of O^T += V^T P^T.
-// O and the sum are rescaled only where a maximum moved.  Bound by the vector units
+// O and the sum are rescaled only where a reference moved.  Bound by the vector units
 // (32 exponentials per lane and tile against 16 matrix instructions).  1500 positions, 20
 // heads: 31.9 us; 70 with two passes over the keys and the probabilities through LDS.
 namespace {
@@ -261,7 +261,15 @@ __global__ void __launch_bounds__(kAThreads) k_enc_attn(EncAttnArgs a) {
   }
   // scores in units of log2(e) / 8, so the exponential is one instruction
   constexpr float kScale = 0.125f * 1.44269504088896340736f;
-  float m = -INFINITY, l = 0.f;  // running maximum (of raw scores) and this lane's share of the sum
+  // Scores are formed less a reference of their query (the products' accumulators start at its
+  // negative, `nref`), so p = 2^(kScale s) with no rounding of the reference in it.  It becomes
+  // the maximum of the first tile with a score above -inf, then moves only when a score
+  // passes it by kRaise: p stays below 2^8
+  constexpr float kRaise = 8.f / kScale;
+  float raise = -INFINITY, l = 0.f;  // l: this lane's share of the sum
+  floatx16 nref;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) nref[v] = 0.f;
   floatx16 o[2];
 #pragma unroll
   for (int nt = 0; nt < 2; ++nt)
@@ -275,8 +283,7 @@ __global__ void __launch_bounds__(kAThreads) k_enc_attn(EncAttnArgs a) {
     floatx16 sc[2];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) sc[kb][v] = 0.f;
+      sc[kb] = nref;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         const int row = kb * 32 + lr;
@@ -298,24 +305,30 @@ __global__ void __launch_bounds__(kAThreads) k_enc_attn(EncAttnArgs a) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sc[kb][v]);
     const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-    const float mn = fmaxf(m, fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1])));  // finite: every tile holds a key
-    if (__builtin_amdgcn_ballot_w64(mn != m)) {
-      const float f = __builtin_amdgcn_exp2f((m - mn) * kScale);  // 0 at the first tile
+    mx = fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1]));
+    if (__builtin_amdgcn_ballot_w64(mx > raise)) {
+      const float d = mx > raise ? mx : 0.f;
+      const float f = raise > 0.f ? __builtin_amdgcn_exp2f(-d * kScale) : 0.f;  // no score yet: l and o are 0
+      if (mx > raise) raise = kRaise;
       l *= f;
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[nt][v] *= f;
-      m = mn;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        sc[0][v] -= d;
+        sc[1][v] -= d;
+        nref[v] -= d;
+      }
     }
-    const float ms = mn * kScale;
     float ls = 0.f;
     uint32_t pk[2][8];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int v = 0; v < 16; v += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[kb][v], kScale, -ms)), p1 = __builtin_amdgcn_exp2f(fmaf(sc[kb][v + 1], kScale, -ms));
+        const float p0 = __builtin_amdgcn_exp2f(sc[kb][v] * kScale), p1 = __builtin_amdgcn_exp2f(sc[kb][v + 1] * kScale);
         ls += p0 + p1;
         pk[kb][v >> 1] = pack2_bf16(p0, p1);
       }

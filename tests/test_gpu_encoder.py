@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 import torch
 
-from encoder_check import encode_and_compare
+from encoder_check import encode_and_compare, rel
 from wf_fixtures import (MICRO, MICRO_ENC, LARGE_V3_ENC, make_encoder_weights, make_audio, make_weights,
                          make_prefix)
 from oracle import OracleOpts
@@ -55,6 +55,37 @@ def test_micro_encoder_matches_oracle():
 @pytest.mark.timeout(900)
 def test_large_v3_encoder_matches_oracle():
     encode_and_compare(LARGE_V3_ENC, 1, std=0.02)
+
+
+def test_scores_of_minus_infinity():
+    """Keys whose scores are -inf have no weight, also where they fill the first tile of 64, and
+    the greatest of the others, 1.3e38, all of it: sound in the first third of the signal makes
+    hidden channel 0 large there, W_k multiplies it past fp32's range, and queries are 1 in
+    that dimension."""
+    ecfg = MICRO_ENC.with_(name="enc-inf", n_ctx=210, d_model=64, n_head=1, n_layer=1, d_ff=64)
+    W = make_encoder_weights(ecfg, std=0.05)
+    V = W.values
+    x = make_audio(ecfg, 0)
+    x[75 * 2 * ecfg.hop:] = 0
+    level = log_mel(x, ecfg.n_mels).sum(0)                     # per frame; two frames per position
+    for name in ("conv1.w", "conv1.b", "conv2.w", "conv2.b", "e0.attn.q.w", "e0.attn.q.b", "e0.attn.k.w"):
+        V[name][:] = 0
+    V["conv1.w"][0, :, 1] = 1
+    V["conv1.b"][0] = bf16(np.float32(-(level[:140].min() + level[160:].max()) / 2))
+    V["conv2.w"][0, 0, 1] = 1
+    V["e0.attn_ln.g"][:], V["e0.attn_ln.b"][:] = 1, 0
+    V["e0.attn.q.b"][0] = 1
+    V["e0.attn.k.w"][0, 0] = bf16(np.float32(-6e37))
+    with np.errstate(over="ignore", invalid="ignore"):
+        E = Encoder(ecfg, V, ENC_OPTS)
+        want = bf16(E.encode(x))
+    from paper_2609_32869_amd import WhisperEncoder
+    enc = WhisperEncoder.from_host(ecfg, [V[n] for n, _ in W.order])
+    got = enc.run(torch.from_numpy(x[None]).cuda()).float().cpu().numpy()[0]
+    enc.close()
+    assert np.isfinite(want).all()
+    print(f"scores of -inf: {rel(got, want):.2e}")
+    assert rel(got, want) <= 1e-2
 
 
 def test_waveform_to_tokens_micro():
